@@ -1,7 +1,8 @@
 // SAP smoother (Sec. 2), domain-resident form for 4^4 domains with FP16 or BF16
-// operands: one workgroup per domain of the launched colour.  The domain's
-// links and odd-site clover inverse (and, in the four-RHS form, its clover term)
-// are staged in LDS once and serve every right-hand side, which the workgroup
+// operands: one workgroup per domain of the launched colour (one per group of
+// right-hand sides on small lattices, see dom_parts).  The domain's links and
+// odd-site clover inverse (and, in the four-RHS form, its clover term) are
+// staged in LDS once and serve every right-hand side of the workgroup, which it
 // takes G at a time: thread (q, j) owns the even site j and the odd site j of
 // right-hand side q of the group.  Two forms (same arithmetic):
 //   G = 4: links, clover and inverse in LDS (141 KB): one workgroup (8 waves) per CU;
@@ -222,6 +223,7 @@ __device__ __forceinline__ void pair_sum3(float& a, float& b, float& c, float (*
 template <typename S, int G, bool CG, bool PERSIST>
 __global__ void __launch_bounds__(kBvh * G) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, const S* __restrict__ cinv, int nrhs,
+          int parts,
           int colour0, int sweeps, int mr_iters, const float2* __restrict__ bvec, float2* __restrict__ xvec) {
   __shared__ S sL[36 * kBv];        // links [mu][9][site]
   __shared__ S sC[CG ? 1 : 36 * kBv];   // clover [36][site] (CG: read from memory instead)
@@ -235,7 +237,8 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
   const int t = threadIdx.x, q = __builtin_amdgcn_readfirstlane(t / kBvh), j = t % kBvh, w = (t / 64) & 1,
             lane = t & 63;
 
-  auto domain = [&](int tile, int colour) {
+  // right-hand sides r_first, r_first + G .. of the groups r_step apart
+  auto domain = [&](int tile, int colour, int r_first, int r_step) {
   const int slot = colour * g.Vch + tile;
   const long long base = (long long)slot * kBv;
 
@@ -273,7 +276,7 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
   cx<float>* X = sX[q];
 
 #pragma unroll 1
-  for (int r0 = 0; r0 < nrhs; r0 += G) {
+  for (int r0 = r_first; r0 < nrhs; r0 += r_step) {
     const int r = r0 + q;
     const bool act = r < nrhs;   // uniform over the two waves of q
     const float2* b = bvec + (long long)(act ? r : 0) * 12 * V;
@@ -399,10 +402,10 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
 
   if constexpr (!PERSIST) {
     // domains of one colour in lexicographic block order, contiguous ranges per XCD
-    int tile, unused;
-    xcd_range_tile(g.Vch, 1, tile, unused);
+    int tile, part;
+    xcd_range_tile(g.Vch, parts, tile, part);
     if (tile >= g.Vch) return;   // uniform per workgroup
-    domain(tile, colour0);
+    domain(tile, colour0, part * G, parts * G);
   } else {
     // gridDim.x is a multiple of 8 and at most Vch; workgroup k of XCD x takes
     // domains k, k + gridDim.x / 8, ... of that XCD's eighth
@@ -415,7 +418,7 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
 #pragma unroll 1
         for (int k = k0; k < per_x; k += nwx) {
           __syncthreads();   // the previous domain's LDS reads are done before the staging overwrites them
-          domain(x8 * per_x + k, colour);
+          domain(x8 * per_x + k, colour, 0, G);
         }
         grid.sync();         // the colour's updates of x are visible to the other colour
       }
@@ -444,6 +447,16 @@ int persist_grid(const GeomDev& g) {
   return n;
 }
 
+// Workgroups per domain: one for all right-hand sides when there are domains
+// enough for several rounds of the chip (each then stages its operator once),
+// one per group of G right-hand sides otherwise.  The chip holds 512 workgroups
+// of the two-RHS form; a group takes 65-85 us and the staging about 3 us, so
+// with few domains the serial loop over the groups leaves CUs idle or ends in a
+// part-filled round.  12 right-hand sides, BF16, us per launch with one / all
+// workgroups per domain: 8 domains (8^4) 401 / 71, 256 (16^3x32) 434 / 265, 864
+// (24^3x32) 1014 / 947, 1296 (24^3x48) 1529 / 1386, 4096 (32^3x64) 4106 / 4153.
+int dom_parts(int ndom, int groups) { return ndom <= 2048 ? groups : 1; }
+
 template <typename S, int G, bool CG>
 void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, const void* b, void* x, bool persist,
              hipStream_t st) {
@@ -460,18 +473,19 @@ void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, c
   const int pg = persist && cs == hipStreamCaptureStatusNone ? persist_grid<S, G, CG>(g) : 0;
   if (pg > 0) {
     GeomDev gg = g;
-    int nr = nrhs, c0 = 0, sw = sweeps, mr_ = mr;
-    void* args[] = {&gg, &L, &C, &I, &nr, &c0, &sw, &mr_, &bb, &xx};
+    int nr = nrhs, pt = 1, c0 = 0, sw = sweeps, mr_ = mr;
+    void* args[] = {&gg, &L, &C, &I, &nr, &pt, &c0, &sw, &mr_, &bb, &xx};
     DD_TIMED("k_sap_dom_persist", st, bytes * 2 * sweeps, flops * 2 * sweeps,
              (void)hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_sap_dom<S, G, CG, true>), dim3(pg),
                                               dim3(kBvh * G), args, 0, st));
     return;
   }
-  const unsigned nb = xcd_grid(g.Vch, 1);
+  const int parts = dom_parts(g.Vch, (nrhs + G - 1) / G);
+  const unsigned nb = xcd_grid(g.Vch, parts);
   for (int s = 0; s < sweeps; ++s)
     for (int colour = 0; colour < 2; ++colour)
       DD_TIMED("k_sap_dom", st, bytes, flops,
-               (k_sap_dom<S, G, CG, false><<<nb, kBvh * G, 0, st>>>(g, L, C, I, nrhs, colour, 1, mr, bb, xx)));
+               (k_sap_dom<S, G, CG, false><<<nb, kBvh * G, 0, st>>>(g, L, C, I, nrhs, parts, colour, 1, mr, bb, xx)));
 }
 
 }  // namespace
