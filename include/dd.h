@@ -133,8 +133,9 @@ typedef struct {
   int32_t sap_wpe;        /* SAP waves per SIMD the registers allow: 2 or 3          */
   int32_t dirac_threads;  /* D apply workgroup size, 64, 128 or 256 (blocks other than 4^4; 4^4 blocks
                              take one 256-thread workgroup per block)                */
-  int32_t coarse_spw;     /* coarse apply: target waves per workgroup, 2, 4 or 8 (sites per workgroup =
-                             max(1, coarse_spw / ceil(2n / 16)), at most 4)          */
+  int32_t coarse_spw;     /* coarse apply on half matrix cores (coarse_mfma_half): target waves per
+                             workgroup, 2, 4 or 8 (sites per workgroup =
+                             max(1, coarse_spw / ceil(2n / 16)), at most 4); other forms ignore it */
   int32_t coarse_half;    /* half-precision setups: coarse blocks in FP16/BF16 (1) or FP32 (0);
                              never changed by dd_autotune */
   int32_t coarse_basis_half; /* FP32 coarse GMRES: Krylov basis stored in FP16 (1) or FP32 (0);

@@ -303,7 +303,7 @@ struct CoarseOps {
   dd_dtype vt;
   int nc;
   const void *Dc, *Dinv;
-  int spw;       // FP32 coarse apply: sites per workgroup
+  int spw;       // half matrix cores: target waves per workgroup
   dd_dtype bt;   // storage of the blocks (FP32 vectors may use FP32, FP16 or BF16 blocks)
   bool hm;          // half blocks on half-precision MFMA
   dd_dtype basis;   // storage of the GMRES basis: vt, or DD_F16 with FP32 vectors
@@ -326,11 +326,24 @@ static CoarseOps coarse_ops(const dd_mg* mg, dd_dtype vt) {
   return c;
 }
 
+// out_o = D_oo^-1 (a_hop D_oe x + beta z) on the odd sites, in one launch where
+// the block form multiplies by the inverse itself (t: scratch otherwise)
+static void odd_solve(const CoarseOps& c, int nrhs, double a_hop, const void* x, double beta, const void* z, void* t,
+                      void* out, hipStream_t st) {
+  const GeomDev& g = *c.g;
+  if (c.hm && (c.bt == DD_F16 || c.bt == DD_BF16)) {
+    launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 0, nrhs, g.Vch, g.Vch, 0.0, nullptr, a_hop, x, beta, z, t, st, c.spw, c.bt, c.hm);
+    launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 1, nrhs, g.Vch, g.Vch, 1.0, t, 0.0, nullptr, 0.0, nullptr, out, st, c.spw, c.bt, c.hm);
+    return;
+  }
+  launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 0, nrhs, g.Vch, g.Vch, 0.0, nullptr, a_hop, x, beta, z, out, st, c.spw,
+                   c.bt, false, true);
+}
+
 // out_e = S v_e = D_ee v_e - D_eo D_oo^-1 D_oe v_e   (t1, t2 scratch, odd parts used)
 static void schur_apply(const CoarseOps& c, int nrhs, const void* v, void* out, void* t1, void* t2, hipStream_t st) {
   const GeomDev& g = *c.g;
-  launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 0, nrhs, g.Vch, g.Vch, 0.0, nullptr, 1.0, v, 0.0, nullptr, t1, st, c.spw, c.bt, c.hm);
-  launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 1, nrhs, g.Vch, g.Vch, 1.0, t1, 0.0, nullptr, 0.0, nullptr, t2, st, c.spw, c.bt, c.hm);
+  odd_solve(c, nrhs, 1.0, v, 0.0, nullptr, t1, t2, st);
   launch_coarse_mv(g, c.vt, c.nc, c.Dc, c.Dinv, 0, nrhs, 0, g.Vch, 1.0, v, -1.0, t2, 0.0, nullptr, out, st, c.spw, c.bt, c.hm);
 }
 
@@ -496,8 +509,7 @@ static dd_status coarse_solve_ops(dd_ctx* ctx, Workspace* w, bool graphs, const 
     if (nfin == nrhs) break;
   }
   // odd sites: y_o = D_oo^-1 (b_o - D_oe y_e)
-  launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 0, nrhs, g.Vch, g.Vch, 0.0, nullptr, -1.0, y, 1.0, b, w->ct1, st, c.spw, c.bt, c.hm);
-  launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 1, nrhs, g.Vch, g.Vch, 1.0, w->ct1, 0.0, nullptr, 0.0, nullptr, y, st, c.spw, c.bt, c.hm);
+  odd_solve(c, nrhs, -1.0, y, 1.0, b, w->ct1, y, st);
   DD_HIP(ctx, hipGetLastError());
   if (iters_out) *iters_out = iters;
   return DD_OK;
@@ -850,8 +862,7 @@ static void coarse_solve_device(dd_mg* mg, Workspace* w, dd_dtype vt, int nrhs, 
     }
   }
   // odd sites: y_o = D_oo^-1 (b_o - D_oe y_e)
-  launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 0, nrhs, g.Vch, g.Vch, 0.0, nullptr, -1.0, y, 1.0, b, w->ct1, st, c.spw, c.bt, c.hm);
-  launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 1, nrhs, g.Vch, g.Vch, 1.0, w->ct1, 0.0, nullptr, 0.0, nullptr, y, st, c.spw, c.bt, c.hm);
+  odd_solve(c, nrhs, -1.0, y, 1.0, b, w->ct1, y, st);
 }
 
 // M v as one graph: restriction, the device-driven coarse solve, prolongation

@@ -14,94 +14,22 @@
 
 namespace {
 
-// One wave per coarse site, lane = row of the 2n x 2n blocks (2n <= 64); NR
-// right-hand sides are accumulated per lane.  The input of the site / its
-// neighbour for the current direction is staged in LDS as [col][rhs], so each
-// lane streams one column of the block (coalesced over the wave) against an
-// LDS broadcast of the inputs: every block element is read once per apply.
-constexpr int kSitesPerWG = 4;
-
-template <typename R, typename Sd, typename Tv, int NR>
-__global__ void __launch_bounds__(64 * kSitesPerWG) k_coarse_mv(GeomDev g, int nc, const Sd* __restrict__ Dc,
-                                                              const Sd* __restrict__ Minv, int use_inv, int nrhs,
-                                                              int site_begin, int count, R a_self,
-                                                              const Tv* __restrict__ xs, R a_hop,
-                                                              const Tv* __restrict__ xh, R beta,
-                                                              const Tv* __restrict__ z, Tv* __restrict__ out,
-                                                              Gate gt) {
-  if (gate_closed(gt)) return;
-  __shared__ cx<R> xsh[kSitesPerWG][64][NR];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int local = blockIdx.x * kSitesPerWG + w;
-  const bool site_ok = local < count;
-  const int X = site_begin + (site_ok ? local : 0);
-  const long long vstride = (long long)g.Vc * nc;   // rhs stride of a coarse vector
-  const bool has_self = a_self != (R)0, has_hop = a_hop != (R)0;
-  const bool row_ok = site_ok && lane < nc;
-  for (int r0 = 0; r0 < nrhs; r0 += NR) {
-    const int nr = nrhs - r0 < NR ? nrhs - r0 : NR;
-    cx<R> acc_s[NR], acc_h[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) acc_s[r] = acc_h[r] = {(R)0, (R)0};
-    for (int d = has_self ? 0 : 1; d < (has_hop ? 9 : 1); ++d) {
-      const int Y = d == 0 ? X : (g.blk_nbr[(d - 1) * g.Vc + X] & DD_SLOT_MASK);
-      const Tv* src = d == 0 ? xs : xh;
-      __syncthreads();
-      if (row_ok)
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-          if (r < nr) xsh[w][lane][r] = ld<R, Tv>(src + (long long)(r0 + r) * vstride + (long long)Y * nc + lane);
-      __syncthreads();
-      if (row_ok) {
-        const Sd* B = d == 0 ? (use_inv ? Minv + (long long)(X - g.Vch) * nc * nc : Dc + (long long)X * 9 * nc * nc)
-                             : Dc + ((long long)X * 9 + d) * nc * nc;
-        cx<R> acc[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) acc[r] = {(R)0, (R)0};
-        for (int c = 0; c < nc; ++c) {
-          cx<R> m = ld<R, Sd>(B + (long long)c * nc + lane);
-#pragma unroll
-          for (int r = 0; r < NR; ++r)
-            if (r < nr) cfma(acc[r], m, xsh[w][c][r]);
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-          if (d == 0) acc_s[r] = acc[r];
-          else acc_h[r] = acc_h[r] + acc[r];
-        }
-      }
-    }
-    if (row_ok)
-#pragma unroll
-      for (int r = 0; r < NR; ++r)
-        if (r < nr) {
-          long long oi = (long long)(r0 + r) * vstride + (long long)X * nc + lane;
-          cx<R> o = a_self * acc_s[r] + a_hop * acc_h[r];
-          if (beta != (R)0) o = o + beta * ld<R, Tv>(z + oi);
-          st<Tv, R>(out + oi, o);
-        }
-  }
-}
-
-// FP32 matrix-core form.  For one coarse site and one direction the stencil
-// term is a complex GEMM Y (2n x NRHS) += B (2n x 2n) X (2n x NRHS).  With
-// B = Br + i Bi, X = Xr + i Xi it is computed as four real 16x16x4 MFMA
-// products per (16-row tile, 4-deep k step): tile C0 collects Y_r = Br Xr - Bi Xi
-// and tile C1 collects Y_i = Br Xi + Bi Xr, with the right-hand side as the
-// column index of both tiles, so each lane ends with the real and imaginary
-// part of the same (row, rhs).  Lane layout of v_mfma_f32_16x16x4f32: A[i][k]
-// at lane i + 16k, B[k][j] at lane j + 16k, D[i][j] at lane j + 16(i/4), value
-// i % 4.  One wave per site, up to 16 right-hand sides per pass, 2n <= 48.
+// Matrix-core form.  For one coarse site and one direction the stencil term is a
+// complex product Y (2n x rhs) += B (2n x 2n) X (2n x rhs) with the right-hand
+// side as the column index, computed by real 16x16x4 MFMAs over (16-row tile,
+// 4-deep k step).  Lane layout: A[i][k] at lane i + 16k, B[k][j] at lane j + 16k;
+// up to 16 right-hand sides per pass, 2n <= 48.
 // Matrix-core order of one NC x NC block (the FP32 and half copies the FP32
 // apply reads).  Element (row, col) lies in row tile t = row / 16 (RT = min(16,
-// NC - 16 t) rows) and k-step ks = col / 4 (lane group lk = col % 4); P
-// consecutive k-steps form a group q = ks / P.  Within a tile the order is
+// NC - 16 t) rows), lane group lk = col / KS and k-step ks = col % KS, with KS =
+// NC / 4 k-steps (so a lane's columns are consecutive, and it reads its part of
+// an input vector with wide loads); P consecutive k-steps form a group q = ks / P.  Within a tile the order is
 // [q][lk][li][e]: lane (li, lk) of the MFMA operand reads its P k-steps of row
 // 16 t + li with one load of P elements, and a wave reads one contiguous stretch.
 // No padding: a block still holds NC * NC elements.
 __host__ __device__ inline long long tiled_off(int row, int col, int NC, int P) {
   const int t = row >> 4, li = row & 15, RT = NC - 16 * t < 16 ? NC - 16 * t : 16;
-  const int ks = col >> 2, lk = col & 3, q = ks / P, e = ks % P;
+  const int KS = NC >> 2, ks = col % KS, lk = col / KS, q = ks / P, e = ks % P;
   return (long long)16 * t * NC + ((long long)(q * 4 + lk) * RT + li) * P + e;
 }
 // P: the largest power of two k-steps per load (at most 16 bytes) that divides NC / 4
@@ -139,108 +67,194 @@ __global__ void k_tile_half(const float2* __restrict__ src, H* __restrict__ dst,
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaMaxNc = 48;
 
-// NC = 2n (a multiple of 4, at most 48).  A workgroup takes S coarse sites with
-// MT = ceil(NC / 16) waves per site, one per 16-row tile of the NC rows: each
-// wave streams its rows of the site's 9 (or 1, or 8) blocks into registers,
-// while the MT waves of the site stage sc * x(Y) for 16 right-hand sides (zero
-// weight past nrhs) in LDS with loads along the columns, one barrier per
-// direction (double-buffered staging).  Complex products use three real MFMAs
-// (Gauss): with A = a + ib and x = c + id,
-//   k1 += a (c + d),  k2 += (a + b)(-d),  k3 += (b - a) c,
-//   Re(A x) = k1 + k2,  Im(A x) = k1 + k3.
-// Site groups are dealt to the XCDs in contiguous eighths, so the neighbours'
-// x of one range come from the same L2.
-template <int NC, int S, typename Sd>
-__global__ void __launch_bounds__(64 * S * ((NC + 15) / 16)) k_coarse_mfma(
+// One accumulator set of a complex product on matrix cores, in FP32 (three real
+// products, Gauss: with A = a + ib and x = c + id, k1 += a (c + d), k2 +=
+// (a + b)(-d), k3 += (b - a) c, Re = k1 + k2, Im = k1 + k3) or FP64 (four real
+// products, chained: the matrix cores are not what bounds it, and the four keep
+// the rounding of the plain form).  row(lk, v): the row that element v of lane
+// group lk holds.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <typename R> struct Cacc;
+template <> struct Cacc<float> {
+  typedef float2 vec;
+  f32x4 k1 = {0.f, 0.f, 0.f, 0.f}, k2 = {0.f, 0.f, 0.f, 0.f}, k3 = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ void add(cx<float> m, float2 x) {
+    k1 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.re, x.x + x.y, k1, 0, 0, 0);
+    k2 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.re + m.im, -x.y, k2, 0, 0, 0);
+    k3 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.im - m.re, x.x, k3, 0, 0, 0);
+  }
+  __device__ __forceinline__ cx<float> get(int v) const { return {k1[v] + k2[v], k1[v] + k3[v]}; }
+  __device__ static int row(int lk, int v) { return 4 * lk + v; }
+};
+template <> struct Cacc<double> {
+  typedef double2 vec;
+  f64x4 kr = {0.0, 0.0, 0.0, 0.0}, ki = {0.0, 0.0, 0.0, 0.0};
+  __device__ __forceinline__ void add(cx<double> m, double2 x) {
+    kr = __builtin_amdgcn_mfma_f64_16x16x4f64(m.re, x.x, kr, 0, 0, 0);
+    ki = __builtin_amdgcn_mfma_f64_16x16x4f64(m.re, x.y, ki, 0, 0, 0);
+    kr = __builtin_amdgcn_mfma_f64_16x16x4f64(-m.im, x.y, kr, 0, 0, 0);
+    ki = __builtin_amdgcn_mfma_f64_16x16x4f64(m.im, x.x, ki, 0, 0, 0);
+  }
+  __device__ __forceinline__ cx<double> get(int v) const { return {kr[v], ki[v]}; }
+  __device__ static int row(int lk, int v) { return lk + 4 * v; }
+};
+
+// NC = 2n (a multiple of 4, at most 48).  A workgroup takes one coarse site with
+// DS groups of MT / TW waves, MT = ceil(NC / 16) row tiles: the groups share out
+// the stencil's directions (group q takes directions d_begin + q, + DS, ...), a
+// wave takes TW row tiles.  It loads its rows of a direction's block and the
+// neighbour's x for 16 right-hand sides straight into matrix-core operand
+// registers (no LDS and no barrier per direction; every load of a direction is
+// issued before its first product, which the compiler would otherwise interleave
+// at half the loads in flight); the groups' sums are added in group order at the
+// end through LDS.  Columns past nrhs and rows past the tile repeat valid ones
+// and are not stored.  NT: the blocks are read past the caches.
+// INV: the result is multiplied by Minv(X) before it is stored (odd-site inverse,
+// loaded before the first direction):
+//   out = Minv (a_self M xs + a_hop sum D_c xh + beta z)
+// which is the odd half of the Schur complement in one launch.
+// Sites go to the XCDs in contiguous eighths, so the neighbours' x of one range
+// come from the same L2.  Bound by the blocks' bytes on large lattices (12
+// right-hand sides, 2n = 40, 24^3x48: 78 -> 71 us, 4.5 TB/s; 32^3x48 4.6 TB/s; one
+// right-hand side 5.1-5.7 TB/s against 4.9 TB/s of a large copy) and by the latency
+// of a launch on small ones (16^3x32, even sites only: 13.7 us before); the form
+// before took one direction at a time through LDS with a barrier for each.
+template <int NC, typename Sd, typename R, bool INV, int DS, int TW, bool NT>
+__global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma(
     GeomDev g, const Sd* __restrict__ Dc, const Sd* __restrict__ Minv, int use_inv, int nrhs, int site_begin,
-    int count, float a_self, const float2* __restrict__ xs, float a_hop, const float2* __restrict__ xh, float beta,
-    const float2* __restrict__ z, float2* __restrict__ out, Gate gt) {
+    int count, R a_self, const typename Cacc<R>::vec* __restrict__ xs, R a_hop,
+    const typename Cacc<R>::vec* __restrict__ xh, R beta, const typename Cacc<R>::vec* __restrict__ z,
+    typename Cacc<R>::vec* __restrict__ out, Gate gt) {
   if (gate_closed(gt)) return;
-  constexpr int MT = (NC + 15) / 16, KS = NC / 4, XP = 17;
-  constexpr int P = tile_group(NC, (int)sizeof(Sd));
+  typedef Cacc<R> Acc;
+  typedef typename Acc::vec Tv;
+  constexpr int MT = (NC + 15) / 16, KS = NC / 4, WG = MT / TW;   // WG: waves per group
+  constexpr bool kTiled = sizeof(R) == 4;   // FP64 blocks are column major
+  constexpr int P = kTiled ? tile_group(NC, (int)sizeof(Sd)) : 1;
   struct alignas(P * sizeof(Sd)) Pack {
     Sd v[P];
   };
-  __shared__ float2 xsh[S][2][NC][XP];
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int s_in = wv / MT, t = wv % MT, tid_site = threadIdx.x - 64 * MT * s_in;
-  const int ngroups = (count + S - 1) / S, per_x = (ngroups + 7) / 8;
-  const int group = (blockIdx.x & 7) * per_x + (blockIdx.x >> 3);
-  if (group >= ngroups) return;   // uniform per workgroup
-  const int local = group * S + s_in;
-  const bool site_ok = local < count;   // S > 1: the last group may be short (its waves still reach the barriers)
-  const int X = site_begin + (site_ok ? local : 0);
-  const int RT = NC - 16 * t < 16 ? NC - 16 * t : 16;
+  struct Rows {
+    Pack a[KS / P];
+  };
+  __shared__ Tv red[DS > 1 ? DS - 1 : 1][MT * 16][16];
+  __shared__ Tv rsh[INV ? NC : 1][INV ? 17 : 1];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int q = wv / WG, t0 = (wv % WG) * TW;
+  const int per_x = (count + 7) / 8;
+  const int local = (blockIdx.x & 7) * per_x + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_x || local >= count) return;   // uniform per workgroup
+  const int X = site_begin + local;
   const long long vstride = (long long)g.Vc * NC;
-  const bool has_self = a_self != 0.f, has_hop = a_hop != 0.f;
+  const int d_begin = a_self != (R)0 ? 0 : 1, d_end = a_hop != (R)0 ? 9 : 1;
   const int li = lane & 15, lk = lane >> 4;
-  const bool row_ok = li < RT;
-  int buf = 0;
+  // rows 16 t + li, columns lk KS + ks of a block
+  auto load_rows = [&](const Sd* B, int t, Rows& r) {
+    const int RT = NC - 16 * t < 16 ? NC - 16 * t : 16, row_c = li < RT ? li : RT - 1;
+#pragma unroll
+    for (int i = 0; i < KS / P; ++i) {
+      if constexpr (kTiled && NT && sizeof(Pack) == 16) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        r.a[i] = __builtin_bit_cast(
+            Pack, __builtin_nontemporal_load(reinterpret_cast<const u4*>(B + 16 * t * NC + ((i * 4 + lk) * RT + row_c) * P)));
+      } else if constexpr (kTiled) {
+        r.a[i] = *reinterpret_cast<const Pack*>(B + 16 * t * NC + ((i * 4 + lk) * RT + row_c) * P);
+      } else {
+        r.a[i].v[0] = B[(lk * KS + i) * NC + 16 * t + row_c];
+      }
+    }
+  };
+  const Sd* Mx = INV || use_inv ? Minv + (long long)(X - g.Vch) * NC * NC : nullptr;
+  // the inverse's row tiles are dealt to the waves in turn
+  constexpr int kWaves = DS * WG, kInvT = INV ? (MT + kWaves - 1) / kWaves : 1;
+  Rows minv[kInvT];
+  if constexpr (INV) {
+#pragma unroll
+    for (int i = 0; i < kInvT; ++i)
+      if (wv + i * kWaves < MT) load_rows(Mx, wv + i * kWaves, minv[i]);
+  }
   for (int r0 = 0; r0 < nrhs; r0 += 16) {
     const int nr = nrhs - r0 < 16 ? nrhs - r0 : 16;
-    const bool rhs_ok = li < nr;
-    f32x4 k1 = {0.f, 0.f, 0.f, 0.f}, k2 = k1, k3 = k1;
-    for (int d = has_self ? 0 : 1; d < (has_hop ? 9 : 1); ++d) {
-      const int Y = d == 0 ? X : (g.blk_nbr[(d - 1) * g.Vc + X] & DD_SLOT_MASK);
-      const float2* src = d == 0 ? xs : xh;
-      const float sc = d == 0 ? a_self : a_hop;
-      const Sd* B = d == 0 ? (use_inv ? Minv + (long long)(X - g.Vch) * NC * NC : Dc + (long long)X * 9 * NC * NC)
-                           : Dc + ((long long)X * 9 + d) * NC * NC;
-      const Sd* Bt = B + (long long)16 * t * NC;
-      // x(Y) first (consecutive threads of the site take consecutive columns; the
-      // loads are clamped into the nr right-hand sides), then this wave's rows of
-      // the block (rows 16t + li, columns 4 ks + lk, P k-steps per load, see
-      // tiled_off), so the staging waits for the x loads only
-      constexpr int XI = (16 * NC + 64 * MT - 1) / (64 * MT);
-      const int nx = nr * NC;
-      float2 xv[XI];
+    const long long roff = (long long)(r0 + (li < nr ? li : nr - 1)) * vstride + lk * KS;
+    cx<R> tot[TW][4];
 #pragma unroll
-      for (int i = 0; i < XI; ++i) {
-        const int e = tid_site + 64 * MT * i, ec = e < nx ? e : nx - 1;
-        const int r = ec / NC, col = ec - r * NC;
-        xv[i] = src[(long long)(r0 + r) * vstride + (long long)Y * NC + col];
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) tot[i][v] = {(R)0, (R)0};
+#pragma unroll 1
+    for (int d = d_begin + q; d < d_end; d += DS) {
+      const int Y = d == 0 ? X : __builtin_amdgcn_readfirstlane(g.blk_nbr[(d - 1) * g.Vc + X] & DD_SLOT_MASK);
+      const Tv* xp = (d == 0 ? xs : xh) + roff + (long long)Y * NC;
+      const Sd* B = d == 0 && use_inv ? Mx : Dc + ((long long)X * 9 + d) * NC * NC;
+      const R sc = d == 0 ? a_self : a_hop;
+      Tv x[KS];
+      Rows rows[TW];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) x[k] = xp[k];
+#pragma unroll
+      for (int i = 0; i < TW; ++i) load_rows(B, t0 + i, rows[i]);
+      __builtin_amdgcn_sched_barrier(0);   // every load is issued before the first product
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        Acc acc;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) acc.add(ld<R, Sd>(&rows[i].a[k / P].v[k % P]), x[k]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tot[i][v] = tot[i][v] + sc * acc.get(v);
       }
-      Pack pk[KS / P];
+    }
+    if constexpr (DS > 1) {
+      if (q > 0)
 #pragma unroll
-      for (int q = 0; q < KS / P; ++q)
-        pk[q] = *reinterpret_cast<const Pack*>(Bt + ((long long)(q * 4 + lk) * RT + (row_ok ? li : 0)) * P);
-      // stage sc * x(Y) as [col][rhs]
+        for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int i = 0; i < XI; ++i) {
-        const int e = tid_site + 64 * MT * i;
-        if (e < nx) {
-          const int r = e / NC, col = e - r * NC;
-          xsh[s_in][buf][col][r] = make_float2(sc * xv[i].x, sc * xv[i].y);
+          for (int v = 0; v < 4; ++v)
+            red[q - 1][16 * (t0 + i) + Acc::row(lk, v)][li] = Tv{tot[i][v].re, tot[i][v].im};
+      __syncthreads();
+    }
+    if (q == 0) {
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = 16 * (t0 + i) + Acc::row(lk, v);
+          cx<R> o = tot[i][v];
+          if constexpr (DS > 1)
+#pragma unroll
+            for (int p = 0; p < DS - 1; ++p) {
+              const Tv b = red[p][row][li];
+              o = o + cx<R>{b.x, b.y};
+            }
+          if (row < NC) {
+            const long long oi = (long long)(r0 + li) * vstride + (long long)X * NC + row;
+            if (li < nr && beta != (R)0) {
+              const Tv zz = z[oi];
+              o = o + beta * cx<R>{zz.x, zz.y};
+            }
+            if constexpr (INV) rsh[row][li] = Tv{o.re, o.im};
+            else if (li < nr) out[oi] = Tv{o.re, o.im};
+          }
         }
-      }
+    }
+    if constexpr (INV) {
       __syncthreads();
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const cx<float> m = row_ok ? ld<float, Sd>(&pk[ks / P].v[ks % P]) : cx<float>{0.f, 0.f};
-        const float2 xb = xsh[s_in][buf][4 * ks + lk][li];
-        const float c = rhs_ok ? xb.x : 0.f, dd = rhs_ok ? xb.y : 0.f;
-        k1 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.re, c + dd, k1, 0, 0, 0);
-        k2 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.re + m.im, -dd, k2, 0, 0, 0);
-        k3 = __builtin_amdgcn_mfma_f32_16x16x4f32(m.im - m.re, c, k3, 0, 0, 0);
-      }
-      buf ^= 1;
-    }
-    if (site_ok && rhs_ok) {
+      for (int i = 0; i < kInvT; ++i) {
+        const int t = wv + i * kWaves;
+        if (t >= MT) break;
+        Acc acc;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = 16 * t + 4 * lk + v;
-        if (row < NC) {
-          long long oi = (long long)(r0 + li) * vstride + (long long)X * NC + row;
-          float2 o = make_float2(k1[v] + k2[v], k1[v] + k3[v]);
-          if (beta != 0.f) {
-            float2 zz = z[oi];
-            o.x += beta * zz.x;
-            o.y += beta * zz.y;
+        for (int k = 0; k < KS; ++k) acc.add(ld<R, Sd>(&minv[i].a[k / P].v[k % P]), rsh[lk * KS + k][li]);
+        if (li < nr)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int row = 16 * t + Acc::row(lk, v);
+            const cx<R> o = acc.get(v);
+            if (row < NC) out[(long long)(r0 + li) * vstride + (long long)X * NC + row] = Tv{o.re, o.im};
           }
-          out[oi] = o;
-        }
       }
     }
+    if constexpr (DS > 1 || INV) __syncthreads();   // red and rsh are refilled by the next 16 right-hand sides
   }
 }
 
@@ -248,7 +262,7 @@ __global__ void __launch_bounds__(64 * S * ((NC + 15) / 16)) k_coarse_mfma(
 // blocks feed 16x16x16 FP16 / BF16 MFMAs directly and sc * x(Y) is rounded to
 // the same type when staged; products accumulate in FP32 (four real MFMAs per
 // complex product: k1 = a c, k2 = b d, k3 = a d, k4 = b c).  MFMA K-slot
-// (lk, v) of K-step s takes column 4 (4 s + v) + lk, so every lane's four A
+// (lk, v) of K-step s takes column lk KS + 4 s + v, so every lane's four A
 // values sit at one (row, lk) of the tiled block layout (see tiled_off);
 // columns past NC are zero on both sides.
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
@@ -371,7 +385,7 @@ __global__ void __launch_bounds__(64 * S * ((NC + 15) / 16)) __attribute__((amdg
           const int e = tid_site + 64 * MT * i;
           if (e < nx) {
             const int r = e / NC, col = e - r * NC;
-            const int ks = col >> 2, cl = col & 3;
+            const int ks = col % KS, cl = col / KS;
             xc[s_in][buf][q][ks >> 2][cl][r][ks & 3] = H::from_f32(sc * xv[q][i].x);
             xd[s_in][buf][q][ks >> 2][cl][r][ks & 3] = H::from_f32(sc * xv[q][i].y);
           }
@@ -424,77 +438,76 @@ __global__ void __launch_bounds__(64 * S * ((NC + 15) / 16)) __attribute__((amdg
   }
 }
 
-typedef void (*MfmaFn)(GeomDev, const void*, const void*, int, int, int, int, float, const float2*, float,
-                       const float2*, float, const float2*, float2*, Gate);
+template <typename R>
+using MfmaFn = void (*)(GeomDev, const void*, const void*, int, int, int, int, R, const typename Cacc<R>::vec*, R,
+                        const typename Cacc<R>::vec*, R, const typename Cacc<R>::vec*, typename Cacc<R>::vec*, Gate);
 
-// spw: target waves per workgroup; sites per workgroup S = max(1, spw / MT), at most 4
-template <int NC, typename Sd, bool HM = false>
-MfmaFn mfma_spw(int spw, unsigned count, dim3& grid, dim3& blk) {
+template <typename R>
+struct MfmaLaunch {
+  MfmaFn<R> fn;
+  dim3 grid, blk;
+};
+
+// half blocks on half matrix cores; spw: target waves per workgroup, sites per workgroup S = max(1, spw / MT), at most 4
+template <int NC, typename Sd>
+MfmaLaunch<float> half_launch(int spw, int count) {
   constexpr int MT = (NC + 15) / 16;
   int S = spw / MT;
-  MfmaFn fn;
-  if (S >= 4) S = 4;
-  else if (S >= 2) S = 2;
-  else S = 1;
-  if constexpr (HM) {
-    fn = S == 4 ? (MfmaFn)k_coarse_mfma_h<NC, 4, Sd> : S == 2 ? (MfmaFn)k_coarse_mfma_h<NC, 2, Sd>
-                                                              : (MfmaFn)k_coarse_mfma_h<NC, 1, Sd>;
-  } else {
-    fn = S == 4 ? (MfmaFn)k_coarse_mfma<NC, 4, Sd> : S == 2 ? (MfmaFn)k_coarse_mfma<NC, 2, Sd>
-                                                            : (MfmaFn)k_coarse_mfma<NC, 1, Sd>;
-  }
-  const unsigned per_x = ((count + S - 1) / S + 7) / 8;   // see k_coarse_mfma
-  grid = dim3(8 * per_x);
-  blk = dim3(64 * S * MT);
-  return fn;
+  S = S >= 4 ? 4 : S >= 2 ? 2 : 1;
+  MfmaFn<float> fn = S == 4 ? (MfmaFn<float>)k_coarse_mfma_h<NC, 4, Sd> : S == 2 ? (MfmaFn<float>)k_coarse_mfma_h<NC, 2, Sd>
+                                                                                 : (MfmaFn<float>)k_coarse_mfma_h<NC, 1, Sd>;
+  const unsigned per_x = ((count + S - 1) / S + 7) / 8;
+  return {fn, dim3(8 * per_x), dim3(64 * S * MT)};
 }
 
-template <typename Sd, bool HM = false>
-MfmaFn mfma_pick(int nc, int spw, unsigned count, dim3& grid, dim3& blk) {
-  switch (nc) {
-    case 12: return mfma_spw<12, Sd, HM>(spw, count, grid, blk);
-    case 16: return mfma_spw<16, Sd, HM>(spw, count, grid, blk);
-    case 24: return mfma_spw<24, Sd, HM>(spw, count, grid, blk);
-    case 32: return mfma_spw<32, Sd, HM>(spw, count, grid, blk);
-    case 40: return mfma_spw<40, Sd, HM>(spw, count, grid, blk);
-    default: return mfma_spw<48, Sd, HM>(spw, count, grid, blk);
-  }
+// Two splits of the full-precision form, by whether the lattice's stencil blocks
+// fit the 256 MB last-level cache:
+//  - they fit: the apply is short and its time a chain of latencies, so a site's
+//    work is spread over four direction groups with one row tile per wave
+//    (at 2n = 40 12 waves per site), and the blocks are kept cached for the next apply;
+//  - they do not: HBM bounds it, so two direction groups whose waves take all
+//    row tiles of a site (its x is loaded once per direction instead of once per
+//    tile) and stream the blocks past the caches.
+// Measured full applies, us, first / second split, 12 right-hand sides, FP32
+// blocks: 2n = 40 on 88 MB (16x16x24x32) 20 / 25, 199 MB (24^3x32) 40 / 49,
+// 299 MB (24^3x48) 76 / 71, 708 MB (32^3x48) 179 / 156; 2n = 48 on 430 MB 111 / 94.
+constexpr double kCachedStencilBytes = 256e6;
+
+template <int NC, typename Sd, typename R>
+MfmaLaunch<R> full_launch(int Vc, int count, bool inv) {
+  constexpr int MT = (NC + 15) / 16;
+  const bool cached = 9.0 * Vc * NC * NC * sizeof(Sd) <= kCachedStencilBytes;
+  MfmaFn<R> fn;
+  if (cached)
+    fn = inv ? (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, true, 4, 1, false> : (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, false, 4, 1, false>;
+  else
+    fn = inv ? (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, true, 2, MT, true> : (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, false, 2, MT, true>;
+  const unsigned per_x = (count + 7) / 8;
+  return {fn, dim3(8 * per_x), dim3(cached ? 64 * 4 * MT : 64 * 2)};
 }
 
-template <typename R, typename Sd, typename Tv>
-void mv(const GeomDev& g, int nc, const void* Dc, const void* Minv, int use_inv, int nrhs, int site_begin, int count,
-        double a_self, const void* xs, double a_hop, const void* xh, double beta, const void* z, void* out,
-        hipStream_t st, int spw, dd_dtype bt, bool hm) {
-  if (count <= 0) return;
-  const int nblocks_read = (a_self != 0.0 ? 1 : 0) + (a_hop != 0.0 ? 8 : 0);
-  const double bytes = (double)count * nblocks_read * nc * nc * sizeof(Sd) +
-                       (double)count * nc * nrhs * sizeof(Tv) * (2 + (beta != 0.0 ? 1 : 0));
-  const double flops = 8.0 * count * nblocks_read * nc * nc * nrhs;
-  const unsigned nb = (unsigned)((count + kSitesPerWG - 1) / kSitesPerWG);
-  const dim3 blk(64 * kSitesPerWG);
-#define DD_MV(NRV)                                                                                                 \
-  DD_TIMED("k_coarse_mv", st, bytes, flops,                                                                        \
-           (k_coarse_mv<R, Sd, Tv, NRV><<<nb, blk, 0, st>>>(g, nc, (const Sd*)Dc, (const Sd*)Minv, use_inv, nrhs,   \
-                                                             site_begin, count, (R)a_self, (const Tv*)xs, (R)a_hop, \
-                                                             (const Tv*)xh, (R)beta, (const Tv*)z, (Tv*)out, \
-                                                             current_gate())))
-  if (sizeof(R) == 4 && nc <= kMfmaMaxNc) {
-    dim3 grid, wg;
-    MfmaFn fn = bt == DD_F16    ? (hm ? mfma_pick<__half2, true>(nc, spw, count, grid, wg)
-                                      : mfma_pick<__half2>(nc, spw, count, grid, wg))
-                : bt == DD_BF16 ? (hm ? mfma_pick<bf16x2, true>(nc, spw, count, grid, wg)
-                                      : mfma_pick<bf16x2>(nc, spw, count, grid, wg))
-                                : mfma_pick<float2>(nc, spw, count, grid, wg);
-    const double hb = bt == DD_F32 ? 1.0 : 0.5;   // half-precision blocks stream half the bytes
-    DD_TIMED("k_coarse_mfma", st, bytes - (1.0 - hb) * (double)count * nblocks_read * nc * nc * sizeof(Sd), flops,
-             (fn<<<grid, wg, 0, st>>>(g, Dc, Minv, use_inv, nrhs, site_begin, count, (float)a_self, (const float2*)xs,
-                                      (float)a_hop, (const float2*)xh, (float)beta, (const float2*)z, (float2*)out,
-                                      current_gate())));
-  } else if (nrhs == 1) DD_MV(1);
-  else if (nrhs <= 4) DD_MV(4);
-  else DD_MV(12);
-#undef DD_MV
+#define DD_NC_SWITCH(nc, CALL)  \
+  switch (nc) {                 \
+    case 12: return CALL(12);   \
+    case 16: return CALL(16);   \
+    case 24: return CALL(24);   \
+    case 32: return CALL(32);   \
+    case 40: return CALL(40);   \
+    default: return CALL(48);   \
+  }
+template <typename Sd, typename R>
+MfmaLaunch<R> full_pick(int nc, int Vc, int count, bool inv) {
+#define DD_FULL(N) (full_launch<N, Sd, R>(Vc, count, inv))
+  DD_NC_SWITCH(nc, DD_FULL)
+#undef DD_FULL
 }
+template <typename Sd>
+MfmaLaunch<float> half_pick(int nc, int count, int spw) {
+#define DD_HALF(N) (half_launch<N, Sd>(spw, count))
+  DD_NC_SWITCH(nc, DD_HALF)
+#undef DD_HALF
+}
+#undef DD_NC_SWITCH
 
 }  // namespace
 
@@ -509,13 +522,29 @@ void launch_coarse_tile(int nc, const double2* src64, long long nblk, float2* ds
 
 void launch_coarse_mv(const GeomDev& g, dd_dtype vt, int nc, const void* Dc, const void* Minv, int use_inv, int nrhs,
                       int site_begin, int count, double a_self, const void* xs, double a_hop, const void* xh,
-                      double beta, const void* z, void* out, hipStream_t st, int spw, dd_dtype bt, bool hm) {
-  if (vt == DD_F64)
-    mv<double, double2, double2>(g, nc, Dc, Minv, use_inv, nrhs, site_begin, count, a_self, xs, a_hop, xh, beta, z, out,
-                                 st, spw, DD_F64, false);
-  else
-    mv<float, float2, float2>(g, nc, Dc, Minv, use_inv, nrhs, site_begin, count, a_self, xs, a_hop, xh, beta, z, out,
-                              st, spw, bt, hm && (bt == DD_F16 || bt == DD_BF16));
+                      double beta, const void* z, void* out, hipStream_t st, int spw, dd_dtype bt, bool hm,
+                      bool post_inv) {
+  if (count <= 0) return;
+  const int nblk = (a_self != 0.0 ? 1 : 0) + (a_hop != 0.0 ? 8 : 0) + (post_inv ? 1 : 0);
+  const double bytes = (double)count * nblk * nc * nc * storage_pair_bytes(bt) +
+                       (double)count * nc * nrhs * vector_pair_bytes(vt) * (2 + (beta != 0.0 ? 1 : 0));
+  const double flops = 8.0 * count * nblk * nc * nc * nrhs;
+  if (vt == DD_F64) {
+    const MfmaLaunch<double> k = full_pick<double2, double>(nc, g.Vc, count, post_inv);
+    DD_TIMED("k_coarse_mv", st, bytes, flops,
+             (k.fn<<<k.grid, k.blk, 0, st>>>(g, Dc, Minv, use_inv, nrhs, site_begin, count, a_self, (const double2*)xs,
+                                             a_hop, (const double2*)xh, beta, (const double2*)z, (double2*)out,
+                                             current_gate())));
+    return;
+  }
+  hm = hm && (bt == DD_F16 || bt == DD_BF16);
+  const MfmaLaunch<float> k = bt == DD_F16    ? (hm ? half_pick<__half2>(nc, count, spw) : full_pick<__half2, float>(nc, g.Vc, count, post_inv))
+                              : bt == DD_BF16 ? (hm ? half_pick<bf16x2>(nc, count, spw) : full_pick<bf16x2, float>(nc, g.Vc, count, post_inv))
+                                              : full_pick<float2, float>(nc, g.Vc, count, post_inv);
+  DD_TIMED("k_coarse_mfma", st, bytes, flops,
+           (k.fn<<<k.grid, k.blk, 0, st>>>(g, Dc, Minv, use_inv, nrhs, site_begin, count, (float)a_self,
+                                           (const float2*)xs, (float)a_hop, (const float2*)xh, (float)beta,
+                                           (const float2*)z, (float2*)out, current_gate())));
 }
 
 // canonical coarse vectors [rhs][lex][nc] complex128 <-> packed [rhs][slot][nc]
