@@ -971,24 +971,30 @@ static dd_status build(dd_mg* mg, hipStream_t st) {
       dd_free(mg->ctx, stage, sizeof(float2) * len);
     }
   }
-  // Galerkin operator from the stored P and the FP64 operator.  W holds `chunk`
-  // FP64 fine vectors (columns of D_c built per pass over P): as many as fit in
+  // Galerkin operator from the stored P and the FP64 operator: directly for 4^4
+  // aggregates, otherwise through FP64 fine vectors.  W holds `chunk` of those
+  // (columns of D_c built per pass over P): as many as fit in
   // 4 GiB, or in half of the budget still free up to 32 GiB, whichever is larger,
   // rounded down to whole 16-column passes of the restriction.  Every column is
   // computed on its own, so the chunk changes the number of passes, not the result.
-  const long long vbytes = 12LL * G.V * (long long)sizeof(double2);
-  const size_t used = ctx_in_use(mg->ctx), free_b = mg->ctx->budget > used ? mg->ctx->budget - used : 0;
-  const size_t wcap = std::max<size_t>(4ULL << 30, std::min<size_t>(free_b / 2, 32ULL << 30));
-  int chunk = (int)std::min<long long>((long long)(wcap / (size_t)vbytes), mg->nc);
-  if (chunk >= 16 && chunk < mg->nc) chunk -= chunk % 16;
-  if (chunk < 1) chunk = 1;
-  double2* W = nullptr;
-  if ((s = dd_alloc(mg->ctx, (void**)&W, (size_t)chunk * vbytes))) {
-    dd_free(mg->ctx, dflag, sizeof(int));
-    return s;
-  }
   const void* Pb = mg->vstore == DD_F64 ? (const void*)mg->P64 : mg->Pst;
-  launch_coarse_build(G, g->ops[DD_F64], mg->vstore, mg->n, Pb, mg->Dc64, W, chunk, st);
+  const long long vbytes = 12LL * G.V * (long long)sizeof(double2);
+  int chunk = 0;
+  double2* W = nullptr;
+  if (galerkin_direct(G)) {
+    launch_galerkin(G, g->ops[DD_F64], mg->vstore, mg->n, Pb, mg->Dc64, st);
+  } else {
+    const size_t used = ctx_in_use(mg->ctx), free_b = mg->ctx->budget > used ? mg->ctx->budget - used : 0;
+    const size_t wcap = std::max<size_t>(4ULL << 30, std::min<size_t>(free_b / 2, 32ULL << 30));
+    chunk = (int)std::min<long long>((long long)(wcap / (size_t)vbytes), mg->nc);
+    if (chunk >= 16 && chunk < mg->nc) chunk -= chunk % 16;
+    if (chunk < 1) chunk = 1;
+    if ((s = dd_alloc(mg->ctx, (void**)&W, (size_t)chunk * vbytes))) {
+      dd_free(mg->ctx, dflag, sizeof(int));
+      return s;
+    }
+    launch_coarse_build(G, g->ops[DD_F64], mg->vstore, mg->n, Pb, mg->Dc64, W, chunk, st);
+  }
   DD_HIP(mg->ctx, hipMemcpyAsync(dflag, &neg, sizeof(int), hipMemcpyHostToDevice, st));
   launch_coarse_invert(G, mg->nc, mg->Dc64, mg->Dinv64, dflag, st);
   const long long ndc = (long long)G.Vc * 9 * mg->nc * mg->nc, ndi = (long long)G.Vch * mg->nc * mg->nc;

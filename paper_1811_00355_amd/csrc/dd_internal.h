@@ -451,6 +451,10 @@ void launch_prolong(const GeomDev& g, dd_dtype vt, dd_dtype pst, int n, const vo
 void launch_gram_schmidt(const GeomDev& g, int n, double2* P, int* bad_flag, hipStream_t st);
 void launch_coarse_build(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P,
                          double2* Dc64, double2* W, int chunk, hipStream_t st);
+// the same without the scratch vectors, for 4^4 aggregates (galerkin_direct)
+bool galerkin_direct(const GeomDev& g);
+void launch_galerkin(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P, double2* Dc64,
+                     hipStream_t st);
 void launch_coarse_invert(const GeomDev& g, int nc, const double2* Dc64, double2* Dinv64, int* bad_flag,
                           hipStream_t st);
 // coarse operator: out = a_self M xs + a_hop sum_d D_c(d) xh(X+d) + beta z on sites [begin, begin+count)
