@@ -102,11 +102,68 @@ __device__ __forceinline__ void clover_mul_stream(const S* C, long long V, long 
   }
 }
 
+// Face halo of a 4^4 block in LDS.  Face f (mu = f >> 1; f even: the hop +mu, f odd:
+// -mu) has 64 sites, one wave: lane p takes the neighbour of the face site whose
+// other three coordinates are the base-4 digits of p, reads its spinor and keeps
+// the projected half spinor (6 entries) of that hop in halo[f][.][p].
+//
+// The halos are read with the block's own spinors, before the operator streams
+// through.  Read where each hop needs them, the lines of the x and y neighbours
+// (which hold few face sites each) had left the L2 by then, although those
+// blocks run on the same XCD at nearly the same time.
+__device__ __forceinline__ int face_pos(int mu, const int l[4]) {
+  // the base-4 digits l[0..3] without digit mu
+  const int all = l[0] | (l[1] << 2) | (l[2] << 4) | (l[3] << 6), low = (1 << (2 * mu)) - 1;
+  return (all & low) | ((all >> 2) & ~low & 63);
+}
+template <int F, typename R, typename Tv>
+__device__ __forceinline__ void face_load(const GeomDev& g, int slot, const Tv* __restrict__ x, int p,
+                                          cx<R> (*halo)[64]) {
+  constexpr int MU = F >> 1;
+  constexpr bool fwd = (F & 1) == 0;
+  SiteLoc s;
+  s.slot = slot;
+  int e = p;
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+    if (d != MU) {
+      s.l[d] = e & 3;
+      e >>= 2;
+    }
+  s.l[MU] = fwd ? 0 : 3;   // the neighbour's coordinate
+  const int nb = g.blk_nbr[(fwd ? MU : 4 + MU) * g.Vc + slot] & DD_SLOT_MASK;
+  const long long J = (long long)nb * 256 + encode_local(g, s.l);
+  cx<R> psi[12], h[6];
+  load_spinor<R, Tv>(x, g.V, J, psi);
+  project<MU, fwd ? -1 : +1, R>(psi, h);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) halo[c][p] = h[c];
+}
+// faces 0 .. NF - 1 of the block, dealt to the four waves of the workgroup
+template <int NF, typename R, typename Tv>
+__device__ __forceinline__ void load_faces(const GeomDev& g, int slot, const Tv* __restrict__ x,
+                                           cx<R> (*halo)[6][64]) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3, p = threadIdx.x & 63;
+#pragma unroll
+  for (int f0 = 0; f0 < NF; f0 += 4) {
+    switch (f0 + w) {
+#define DD_FACE(F) \
+  case F:          \
+    if constexpr (F < NF) face_load<F, R, Tv>(g, slot, x, p, halo[F]); \
+    break;
+      DD_FACE(0) DD_FACE(1) DD_FACE(2) DD_FACE(3) DD_FACE(4) DD_FACE(5) DD_FACE(6) DD_FACE(7)
+#undef DD_FACE
+      default: break;
+    }
+  }
+}
+
 // The eight hops in the order of hop_all (forward then backward per direction),
 // with both links of a direction loaded together: the backward neighbour's
 // forward link U_mu(x - mu) lies, for most sites, in the lines the workgroup's
 // own forward loads have just fetched, which the L2 does not keep until a
-// later backward hop once many blocks stream through it.
+// later backward hop once many blocks stream through it.  fetch(k, J, inside,
+// psi) gives the neighbour's spinor, or its half spinor with zero lower spins.
 template <typename R, typename S, typename Fetch>
 __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, const SiteLoc& s, long long I,
                                           Fetch fetch, cx<R>* acc) {
@@ -118,7 +175,7 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
     cx<R> uf[9], ub[9], psi[12];
     load_link<R, S>(links, g.V, mu, I, uf);
     load_link<R, S>(links, g.V, mu, Jb, ub);
-    fetch(Jf, inf, psi);
+    fetch(2 * mu, Jf, inf, psi);
     const R cf = (R)1 * (R)(wf ? -0.5 * g.bc_t : -0.5);
     switch (mu) {
       case 0: hop_t<0, -1, false, R>(uf, psi, cf, acc); break;
@@ -126,7 +183,7 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
       case 2: hop_t<2, -1, false, R>(uf, psi, cf, acc); break;
       default: hop_t<3, -1, false, R>(uf, psi, cf, acc); break;
     }
-    fetch(Jb, inb, psi);
+    fetch(2 * mu + 1, Jb, inb, psi);
     const R cb = (R)1 * (R)(wb ? -0.5 * g.bc_t : -0.5);
     switch (mu) {
       case 0: hop_t<0, +1, true, R>(ub, psi, cb, acc); break;
@@ -138,15 +195,20 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
 }
 
 // Block form (4^4 blocks: one workgroup of Bv = 256 threads per block and
-// right-hand side).  The block's spinors are staged in LDS once; hops to sites
-// of the same block read them there, so memory sees one read of every spinor
-// plus the hops across the block faces (a quarter of the sites per direction),
-// instead of eight gathers per site that the L2 cannot hold between hops.
-template <typename R, typename S, typename Tv, typename To = Tv, bool NT = false>
+// right-hand side).  The block's spinors and its first NF faces' half spinors
+// are staged in LDS once; hops read them there, so memory sees one read of every
+// spinor plus the faces.  NF (see blk_launch) is what leaves the CU its workgroups:
+// all eight faces in FP32 (48 KB), x and y in FP64 (72 KB; the z and t faces are whole
+// lines, and their blocks run far apart in the slab order).  Bound by traffic:
+// at 32^3x64, FP64, twelve right-hand sides, 32 GB a launch (2.7 times the algorithmic
+// bytes) at 5.3 TB/s; two right-hand sides of a block in one workgroup measured
+// slower (7.2 against 6.1 ms).
+template <typename R, typename S, typename Tv, typename To, bool NT, int NF>
 __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restrict__ links,
                                                    const S* __restrict__ clov, int nrhs, const Tv* __restrict__ in,
                                                    To* __restrict__ out) {
   __shared__ cx<R> sp[12][256];
+  __shared__ cx<R> halo[NF ? NF : 1][6][64];
   int tile, r;
   if (!xcd_slab_tile(g, 1, nrhs, tile, r)) return;   // uniform per workgroup
   const long long base = (long long)tile * 256;
@@ -157,14 +219,21 @@ __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restric
   load_spinor<R, Tv>(x, g.V, I, psi);
 #pragma unroll
   for (int c = 0; c < 12; ++c) sp[c][threadIdx.x] = psi[c];
+  load_faces<NF, R, Tv>(g, tile, x, halo);
   __syncthreads();
   if constexpr (NT) clover_mul_stream<R, S>(clov, g.V, I, psi, acc);
   else clover_mul<R, S, false>(clov, g.V, I, psi, acc);
-  auto fetch = [&](long long J, bool inside, cx<R>* p) {
+  auto fetch = [&](int k, long long J, bool inside, cx<R>* p) {
     if (inside) {
       const int j = (int)(J - base);
 #pragma unroll
       for (int c = 0; c < 12; ++c) p[c] = sp[c][j];
+    } else if (k < NF) {
+      const int q = face_pos(k >> 1, s.l);
+#pragma unroll
+      for (int c = 0; c < 6; ++c) p[c] = halo[k][c][q];
+#pragma unroll
+      for (int c = 6; c < 12; ++c) p[c] = {(R)0, (R)0};
     } else {
       load_spinor<R, Tv>(x, g.V, J, p);
     }
@@ -291,28 +360,33 @@ constexpr double kDiracFlopsPerSite = 1320.0 + 504.0 + 24.0;
 
 }  // namespace
 
-// block form of every storage type; NT: streaming clover and output (one right-hand side)
-template <bool NT>
+// Block form.  With one right-hand side the clover and the output are streamed.
+// Faces in LDS: x and y in FP64, all in FP32, none for half operands (their launch
+// moves half the bytes, and the halos gave nothing) and none on lattices of at
+// most 256 blocks, which run together anyway, so that the faces would be one more
+// latency.  (By the lattice and not by the launch: the two forms round differently,
+// and a right-hand side has the same bits in every batch.)  us, without / with faces:
+// FP64 32^3x64 one right-hand side 733 / 697, twelve 6522 / 6125; FP32 24^3x48 113 / 103,
+// twelve 1148 / 1055; 8^4 FP32 13.1 / 14.1, FP64 14.1 / 15.8.
+template <typename R, typename S, typename Tv, typename To>
+void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, void* out, hipStream_t st) {
+  const unsigned nb = xcd_grid(g.Vc, nrhs);
+  const S* L = (const S*)ops.links;
+  const S* C = (const S*)ops.clover;
+  constexpr int NF = sizeof(R) == 8 ? 4 : sizeof(S) == 8 ? 8 : 0;
+  const bool few = g.Vc <= 256;
+  auto* fn = nrhs == 1 ? (few ? k_dirac_blk<R, S, Tv, To, true, 0> : k_dirac_blk<R, S, Tv, To, true, NF>)
+                       : (few ? k_dirac_blk<R, S, Tv, To, false, 0> : k_dirac_blk<R, S, Tv, To, false, NF>);
+  fn<<<nb, 256, 0, st>>>(g, L, C, nrhs, (const Tv*)in, (To*)out);
+}
+
 static void blk_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, const void* in, void* out,
                          hipStream_t st) {
-  const unsigned nb = xcd_grid(g.Vc, nrhs);
   switch (dt) {
-    case DD_F64:
-      k_dirac_blk<double, double2, double2, double2, NT><<<nb, 256, 0, st>>>(
-          g, (const double2*)ops.links, (const double2*)ops.clover, nrhs, (const double2*)in, (double2*)out);
-      break;
-    case DD_F32:
-      k_dirac_blk<float, float2, float2, float2, NT><<<nb, 256, 0, st>>>(
-          g, (const float2*)ops.links, (const float2*)ops.clover, nrhs, (const float2*)in, (float2*)out);
-      break;
-    case DD_F16:
-      k_dirac_blk<float, __half2, float2, float2, NT><<<nb, 256, 0, st>>>(
-          g, (const __half2*)ops.links, (const __half2*)ops.clover, nrhs, (const float2*)in, (float2*)out);
-      break;
-    case DD_BF16:
-      k_dirac_blk<float, bf16x2, float2, float2, NT><<<nb, 256, 0, st>>>(
-          g, (const bf16x2*)ops.links, (const bf16x2*)ops.clover, nrhs, (const float2*)in, (float2*)out);
-      break;
+    case DD_F64: blk_launch<double, double2, double2, double2>(g, ops, nrhs, in, out, st); break;
+    case DD_F32: blk_launch<float, float2, float2, float2>(g, ops, nrhs, in, out, st); break;
+    case DD_F16: blk_launch<float, __half2, float2, float2>(g, ops, nrhs, in, out, st); break;
+    case DD_BF16: blk_launch<float, bf16x2, float2, float2>(g, ops, nrhs, in, out, st); break;
   }
 }
 
@@ -330,10 +404,7 @@ static void dirac_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int 
     return;
   }
   if (g.Bv == 256 && g.Vc % 16 == 0) {   // block form, slab order over the blocks
-    if (nrhs == 1)
-      blk_dispatch<true>(g, dt, ops, nrhs, in, out, st);
-    else
-      blk_dispatch<false>(g, dt, ops, nrhs, in, out, st);
+    blk_dispatch(g, dt, ops, nrhs, in, out, st);
     return;
   }
   if (threads != 64 && threads != 128) threads = 256;
@@ -374,14 +445,8 @@ void launch_dirac_f32_in(const GeomDev& g, const OpSet& ops64, int nrhs, const f
   const double2* L = (const double2*)ops64.links;
   const double2* C = (const double2*)ops64.clover;
   if (g.Bv == 256 && g.Vc % 16 == 0) {
-    if (nrhs == 1)
-      DD_TIMED("k_dirac", st, bytes, flops,
-               (k_dirac_blk<double, double2, float2, double2, true><<<xcd_grid(g.Vc, nrhs), 256, 0, st>>>(
-                   g, L, C, nrhs, in, out)));
-    else
-      DD_TIMED("k_dirac", st, bytes, flops,
-               (k_dirac_blk<double, double2, float2, double2, false><<<xcd_grid(g.Vc, nrhs), 256, 0, st>>>(
-                   g, L, C, nrhs, in, out)));
+    DD_TIMED("k_dirac", st, bytes, flops,
+             (blk_launch<double, double2, float2, double2>(g, ops64, nrhs, in, out, st)));
     return;
   }
   if (threads != 64 && threads != 128) threads = 256;
