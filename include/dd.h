@@ -124,7 +124,7 @@ const char* dd_last_error(const dd_ctx* ctx);
 size_t dd_ctx_bytes_in_use(const dd_ctx* ctx);
 void dd_mg_params_default(dd_mg_params* p);
 
-/* Launch shapes and coarse storage.  The first three give bit-identical results
+/* Launch shapes and coarse storage.  The launch shapes give bit-identical results
  * for every choice (see dd_autotune).  coarse_half, coarse_basis_half and
  * coarse_mfma_half change the rounding of the coarse-level arithmetic, which
  * only the FGMRES outer iteration count can see (the outer solver is flexible,
@@ -144,12 +144,13 @@ typedef struct {
                                 FP16 / BF16 matrix cores with x rounded to the same type and FP32
                                 accumulation (1), or convert them to FP32 (0); never changed by
                                 dd_autotune */
-  int32_t sap_dom_rhs;       /* SAP on 4^4 domains with FP16 / BF16 operands: one workgroup per domain,
-                                its operator staged in LDS once and shared by the right-hand sides,
-                                taken 2 at a time (links and inverse in LDS, two workgroups per CU) or
-                                4 at a time (clover in LDS too, one per CU); 0 = one workgroup per
-                                (domain, RHS) in layout sap_wpe.  Same arithmetic, rounding may differ
-                                in the last place. */
+  int32_t sap_dom_rhs;       /* SAP on 4^4 domains with FP32, FP16 or BF16 operands: workgroups with the
+                                domain's operator staged in LDS, shared by the right-hand sides; half
+                                operands 2 at a time (links and inverse in LDS, two workgroups per CU)
+                                or 4 at a time (clover in LDS too, one per CU), FP32 operands 4 at a
+                                time for either value (a single right-hand side on more than 512
+                                domains per colour runs as for 0); 0 = one workgroup per (domain, RHS)
+                                in layout sap_wpe.  Same bits. */
   int32_t sap_persist;       /* with sap_dom_rhs > 0: every sweep and colour of a smoother application in
                                 one cooperative launch whose workgroups (as many as the CUs hold) meet
                                 at a grid barrier between colours (1), or one launch per colour (0).

@@ -337,7 +337,7 @@ struct OpSet {
 struct Tuning {
   int sap_wpe = 2;          // SAP layout: 2 (registers, 2 waves per SIMD) or 3 (lean LDS, 3)
   int sap_persist = 0;      // domain-resident SAP: all sweeps in one cooperative launch (same bits)
-  int sap_dom_rhs = 2;      // 4^4 domains, FP16/BF16 operands: RHS per workgroup of the domain-resident
+  int sap_dom_rhs = 2;      // 4^4 domains, FP32/FP16/BF16 operands: RHS per workgroup of the domain-resident
                             // SAP (operator staged in LDS once per domain), 2 or 4; 0 = one workgroup per
                             // (domain, RHS)
   int dirac_threads = 256;  // D apply workgroup size: 64, 128 or 256
@@ -440,6 +440,7 @@ void launch_dirac_f32_in(const GeomDev& g, const OpSet& ops64, int nrhs, const f
 void launch_sap(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                 const void* b, void* x, int wpe, int dom_rhs, int persist, hipStream_t st);
 bool sap_dom_supported(const GeomDev& g, dd_dtype dt);
+bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs);   // supported and the better form
 void launch_sap_dom(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                     const void* b, void* x, int rhs_group, bool persist, hipStream_t st);
 // transfer and coarse construction

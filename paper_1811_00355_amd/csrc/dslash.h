@@ -84,6 +84,24 @@ __device__ __forceinline__ void cfma4_conj(cx<R>& acc, cx<R> a, cx<R> b) {
   acc.im = fma(-a.im, b.re, acc.im);
 }
 
+// a * b and conj(a) * b with the contraction spelled out, so that every kernel
+// (whatever the compiler would fuse in its context) rounds the same
+template <typename R>
+__device__ __forceinline__ cx<R> cmul2(cx<R> a, cx<R> b) {
+  return {fma(-a.im, b.im, a.re * b.re), fma(a.im, b.re, a.re * b.im)};
+}
+template <typename R>
+__device__ __forceinline__ cx<R> cmul2_conj(cx<R> a, cx<R> b) {
+  return {fma(a.im, b.im, a.re * b.re), fma(-a.im, b.re, a.re * b.im)};
+}
+// (re, im) += conj(p) r and pp += |p|^2, the sums of a minimal-residual step
+template <typename R>
+__device__ __forceinline__ void mr_sums(cx<R> p, cx<R> r, R& re, R& im, R& pp) {
+  re = fma(p.im, r.im, fma(p.re, r.re, re));
+  im = fma(-p.im, r.re, fma(p.re, r.im, im));
+  pp = fma(p.im, p.im, fma(p.re, p.re, pp));
+}
+
 // o = U h on both spin components of a half spinor
 template <typename R>
 __device__ __forceinline__ void su3_mul_half(const cx<R>* u, const cx<R>* h, cx<R>* o) {
@@ -91,7 +109,7 @@ __device__ __forceinline__ void su3_mul_half(const cx<R>* u, const cx<R>* h, cx<
   for (int s = 0; s < 2; ++s)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      cx<R> acc = u[3 * a] * h[3 * s];
+      cx<R> acc = cmul2(u[3 * a], h[3 * s]);
       cfma4(acc, u[3 * a + 1], h[3 * s + 1]);
       cfma4(acc, u[3 * a + 2], h[3 * s + 2]);
       o[3 * s + a] = acc;
@@ -104,7 +122,7 @@ __device__ __forceinline__ void su3_dag_mul_half(const cx<R>* u, const cx<R>* h,
   for (int s = 0; s < 2; ++s)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      cx<R> acc = cmul_conj(u[a], h[3 * s]);
+      cx<R> acc = cmul2_conj(u[a], h[3 * s]);
       cfma4_conj(acc, u[3 + a], h[3 * s + 1]);
       cfma4_conj(acc, u[6 + a], h[3 * s + 2]);
       o[3 * s + a] = acc;

@@ -1,5 +1,5 @@
-// SAP smoother (Sec. 2), domain-resident form for 4^4 domains with FP16 or BF16
-// operands: one workgroup per domain of the launched colour (one per group of
+// SAP smoother (Sec. 2), domain-resident form for 4^4 domains with FP32, FP16 or
+// BF16 operands: one workgroup per domain of the launched colour (one per group of
 // right-hand sides on small lattices, see dom_parts).  The domain's links and
 // odd-site clover inverse (and, in the four-RHS form, its clover term) are
 // staged in LDS once and serve every right-hand side of the workgroup, which it
@@ -9,7 +9,10 @@
 //   G = 2: links and inverse in LDS (80 KB), the clover read from memory (L2):
 //          two domains' workgroups share a CU, so one's memory waits overlap
 //          the other's arithmetic.
-// The arithmetic is that of the per-RHS kernel in sap.hip:
+// FP32 operands take G = 4 with the clover from memory (156 KB): 16^3x32, three
+// right-hand sides 126 -> 89 us per launch, 32^3x64, twelve 6.49 -> 4.81 ms against the
+// per-RHS kernel, whose links come from L2 one hop at a time.
+// The arithmetic is that of the per-RHS kernel in sap.hip, bit for bit:
 //   r_B   = b - D x on the domain (halo of x from the other colour's domains)
 //   rhs_e = r_e - H_eo A_oo^-1 r_o            (H: hops inside the domain)
 //   MR on S = A_ee - H_eo A_oo^-1 H_oe from e_e = 0, k steps
@@ -123,6 +126,7 @@ __device__ __forceinline__ cx<float> unpack(__half2 v) {
   const float2 f = __half22float2(v);
   return {f.x, f.y};
 }
+__device__ __forceinline__ cx<float> unpack(float2 v) { return {v.x, v.y}; }
 __device__ __forceinline__ cx<float> unpack(bf16x2 v) {
   return {__uint_as_float(v.u << 16), __uint_as_float(v.u & 0xffff0000u)};
 }
@@ -296,9 +300,9 @@ __global__ void __launch_bounds__(kBvh * G) __attribute__((amdgpu_waves_per_eu(2
 k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, const S* __restrict__ cinv, int nrhs,
           int parts,
           int colour0, int sweeps, int mr_iters, const float2* __restrict__ bvec, float2* __restrict__ xvec) {
-  __shared__ S sL[36 * kBv];        // links [mu][9][site]
-  __shared__ S sC[CG ? 1 : 36 * kBv];   // clover [36][site] (CG: read from memory instead)
-  __shared__ S sI[36 * kBvh];       // inverse of the odd sites [36][half index]
+  __shared__ __align__(16) S sL[36 * kBv];        // links [mu][9][site]
+  __shared__ __align__(16) S sC[CG ? 1 : 36 * kBv];   // clover [36][site] (CG: read from memory instead)
+  __shared__ __align__(16) S sI[36 * kBvh];       // inverse of the odd sites [36][half index]
   __shared__ cx<float> sX[G][12 * kBvh];   // per right-hand side: one half-domain spinor field
   __shared__ float red[G][2][4];
 
@@ -317,7 +321,8 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
   // 36 rows of 128 (odd inverse), in 16-byte pieces, all loads issued before the
   // LDS writes
   {
-    constexpr int kRowQ = kBv / 4, kRowQh = kBvh / 4;             // 16-byte pieces per row
+    constexpr int kEl = 16 / (int)sizeof(S);                      // elements per 16-byte piece
+    constexpr int kRowQ = kBv / kEl, kRowQh = kBvh / kEl;         // pieces per row
     constexpr int kNL = 36 * kRowQ, kNI = 36 * kRowQh;            // pieces per field
     constexpr int kNF = CG ? 1 : 2;                               // full-domain fields staged
     constexpr int kTot = kNF * kNL + kNI;
@@ -329,7 +334,7 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
       const int f = e < kNL ? 0 : (e < kNF * kNL ? 1 : 2), r = e < kNF * kNL ? e - f * kNL : e - kNF * kNL;
       const int row = f < 2 ? r / kRowQ : r / kRowQh, q4 = f < 2 ? r % kRowQ : r % kRowQh;
       const S* src = f == 0 ? links : f == 1 ? clov : cinv;
-      const long long gi = (long long)row * V + base + (f == 2 ? kBvh : 0) + 4 * q4;
+      const long long gi = (long long)row * V + base + (f == 2 ? kBvh : 0) + kEl * q4;
       if (e < kTot) v[i] = *reinterpret_cast<const u32x4*>(src + gi);
     }
 #pragma unroll
@@ -337,7 +342,7 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
       const int e = t + i * kBvh * G;
       const int f = e < kNL ? 0 : (e < kNF * kNL ? 1 : 2), r = e < kNF * kNL ? e - f * kNL : e - kNF * kNL;
       S* dst = f == 0 ? sL : f == 1 ? sC : sI;
-      if (e < kTot) *reinterpret_cast<u32x4*>(dst + 4 * r) = v[i];
+      if (e < kTot) *reinterpret_cast<u32x4*>(dst + kEl * r) = v[i];
     }
   }
   unsigned elo, ehi, olo, ohi;
@@ -439,12 +444,7 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
         else clover_lds<S, kBv>(sC + j, rho, tt);
         hops_inside<S, 0>(sL, j, elo, ehi, X, -1.f, tt);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-          const cx<float> z = cmul_conj(tt[c], rho[c]);   // conj(p) rho
-          pr_re += z.re;
-          pr_im += z.im;
-          pp += tt[c].re * tt[c].re + tt[c].im * tt[c].im;
-        }
+        for (int c = 0; c < 12; ++c) mr_sums(tt[c], rho[c], pr_re, pr_im, pp);   // conj(p) rho
       }
       pair_sum3(pr_re, pr_im, pp, red, q, w, lane);
       if (act) {
@@ -452,8 +452,8 @@ k_sap_dom(GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, co
         if (pp > 0.f) alpha = {pr_re / pp, pr_im / pp};
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-          cfma(e[c], alpha, rho[c]);
-          rho[c] = rho[c] - alpha * tt[c];
+          cfma4(e[c], alpha, rho[c]);
+          cfma4(rho[c], -alpha, tt[c]);
         }
       }
     }
@@ -570,14 +570,24 @@ void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, c
 
 }  // namespace
 
+// FP32 operands, one right-hand side on lattices of several rounds of domains: three
+// of the form's four right-hand-side slots would idle, and the per-RHS kernel
+// (the same bits) keeps more domains on a CU.  us per launch, per RHS / domain form:
+// 24^3x48 one right-hand side 340 / 407, four 787 / 625; 16^3x32 104 / 67.
+bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs) {
+  return sap_dom_supported(g, dt) && !(dt == DD_F32 && nrhs == 1 && g.Vch > 512);
+}
+
 bool sap_dom_supported(const GeomDev& g, dd_dtype dt) {
-  return (dt == DD_F16 || dt == DD_BF16) && g.b[0] == kE && g.b[1] == kE && g.b[2] == kE && g.b[3] == kE &&
+  return (dt == DD_F32 || dt == DD_F16 || dt == DD_BF16) && g.b[0] == kE && g.b[1] == kE && g.b[2] == kE && g.b[3] == kE &&
          g.Vch % 8 == 0;
 }
 
 void launch_sap_dom(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                     const void* b, void* x, int rhs_group, bool persist, hipStream_t st) {
-  if (rhs_group == 2) {
+  if (dt == DD_F32) {   // links, inverse and four right-hand sides' vectors fill a CU's LDS
+    run_dom<float2, 4, true>(g, ops, nrhs, sweeps, mr_iters, b, x, persist, st);
+  } else if (rhs_group == 2) {
     if (dt == DD_F16) run_dom<__half2, 2, true>(g, ops, nrhs, sweeps, mr_iters, b, x, persist, st);
     else run_dom<bf16x2, 2, true>(g, ops, nrhs, sweeps, mr_iters, b, x, persist, st);
   } else {
