@@ -57,7 +57,20 @@ struct Arnoldi {
     kcyc = a.take<int>(nrhs);
     finished = a.take<int>(nrhs);
   }
+  // the per-RHS status (tolabs, beta, est, active, kcyc, finished) lies together: one copy fetches it
+  size_t status_bytes(int nrhs) const {
+    return (const char*)(finished + nrhs) - (const char*)tolabs;
+  }
+  // host copy of one of the status arrays
+  template <typename T>
+  const T* in_status(const char* host, const T* dev) const {
+    return reinterpret_cast<const T*>(host + ((const char*)dev - (const char*)tolabs));
+  }
 };
+// bytes of the status of nrhs right-hand sides as carve() lays it out (256-byte pieces)
+constexpr size_t status_capacity(int nrhs) {
+  return 3 * (((size_t)nrhs * sizeof(double) + 255) & ~size_t(255)) + 3 * (((size_t)nrhs * sizeof(int) + 255) & ~size_t(255));
+}
 
 struct Workspace {
   int nrhs = 0;
@@ -83,8 +96,7 @@ struct Workspace {
   double* partial;
   int* citers = nullptr;   // coarse Arnoldi steps of the device-driven solves (whole-M graphs)
   double2* mr = nullptr;   // minimal-residual smoother of a third level: <Ar, r>, <Ar, Ar>, alpha per RHS
-  int* hflags = nullptr;   // pinned host mirror: active[nrhs], kcyc[nrhs]
-  double* hvals = nullptr; // pinned host mirror: est[nrhs], tolabs[nrhs], nrm[nrhs]
+  char* hstat = nullptr;   // pinned host mirror of an Arnoldi status
   // captured coarse GMRES chunks, keyed by (nrhs, dtype, basis dtype, block dtype, waves per workgroup,
   // half matrix cores, first iteration, length, ends cycle), i.e. every launch choice baked into a capture;
   // they hold this arena's addresses and die with it
@@ -177,8 +189,7 @@ static size_t ws_bytes(const WsShape& sh, int nrhs, bool outer) {
 static void destroy_ws(dd_ctx* ctx, Workspace* w) {
   if (!w) return;
   dd_free(ctx, w->arena.base, w->arena.cap);
-  if (w->hflags) (void)hipHostFree(w->hflags);
-  if (w->hvals) (void)hipHostFree(w->hvals);
+  if (w->hstat) (void)hipHostFree(w->hstat);
   for (auto& kv : w->graphs) (void)hipGraphExecDestroy(kv.second.exec);
   for (auto& kv : w->mgraphs) (void)hipGraphExecDestroy(kv.second.exec);
   if (w->cap) (void)hipStreamDestroy(w->cap);
@@ -211,8 +222,7 @@ static dd_status alloc_ws(dd_ctx* ctx, int nrhs, Carve carve, Workspace** out) {
   (void)hipMemset(w->arena.base, 0, bytes);
   w->arena.used = 0;
   carve(*w);
-  if (hipHostMalloc((void**)&w->hflags, sizeof(int) * 2 * nrhs) != hipSuccess ||
-      hipHostMalloc((void**)&w->hvals, sizeof(double) * 3 * nrhs) != hipSuccess) {
+  if (hipHostMalloc((void**)&w->hstat, status_capacity(nrhs)) != hipSuccess) {
     destroy_ws(ctx, w);
     return dd_fail(ctx, DD_ENOMEM, "pinned host buffers");
   }
@@ -240,21 +250,21 @@ static dd_status ensure_ws(dd_mg* mg, int nrhs, bool outer) {
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
-static int count_active(Workspace* w, const int* dev_active, int nrhs, hipStream_t st) {
-  (void)hipMemcpyAsync(w->hflags, dev_active, sizeof(int) * nrhs, hipMemcpyDeviceToHost, st);
+// the status of nrhs right-hand sides in w->hstat; returns how many are active
+static int fetch_status(Workspace* w, const Arnoldi& a, int nrhs, hipStream_t st) {
+  (void)hipMemcpyAsync(w->hstat, a.tolabs, a.status_bytes(nrhs), hipMemcpyDeviceToHost, st);
   (void)hipStreamSynchronize(st);
+  const int* act = a.in_status(w->hstat, a.active);
   int c = 0;
-  for (int r = 0; r < nrhs; ++r) c += w->hflags[r] != 0;
+  for (int r = 0; r < nrhs; ++r) c += act[r] != 0;
   return c;
 }
-
-// longest cycle over the RHS (kcyc copied to hflags[nrhs..2 nrhs))
-static int max_kcyc(Workspace* w, Arnoldi& a, int nrhs, hipStream_t st) {
-  (void)hipMemcpyAsync(w->hflags + nrhs, a.kcyc, sizeof(int) * nrhs, hipMemcpyDeviceToHost, st);
-  (void)hipStreamSynchronize(st);
-  int k = 0;
-  for (int r = 0; r < nrhs; ++r) k = w->hflags[nrhs + r] > k ? w->hflags[nrhs + r] : k;
-  return k;
+// longest cycle over the right-hand sides in the last fetched status
+static int longest_cycle(const Workspace* w, const Arnoldi& a, int nrhs) {
+  const int* k = a.in_status(w->hstat, a.kcyc);
+  int m = 0;
+  for (int r = 0; r < nrhs; ++r) m = k[r] > m ? k[r] : m;
+  return m;
 }
 
 // squared norms of nrhs vectors (count entries at stride ld) into out[r].x
@@ -293,6 +303,23 @@ static void cgs(Workspace* ws, Arnoldi& a, dd_dtype vt, int nrhs, long long coun
   }
   launch_multi_axpy(bt, vt, nrhs, count, ld, V, nv, vstride, a.h1, a.m + 1, 0, -1.0, w, st);
   launch_dots(vt, vt, nrhs, count, ld, w, 1, 0, w, ws->partial, nblk, a.nrm2, 1, 0, st);
+}
+
+// Arnoldi step j from w = A v_j: Gram-Schmidt, Hessenberg column and rotation, and (next set) v_{j+1} = w / |w| into
+// `next`, with its FP32 copy where asked
+static void arnoldi_step(Workspace* ws, Arnoldi& a, dd_dtype vt, int nrhs, long long count, long long ld,
+                         const void* V, long long vstride, int j, void* w, int passes, void* next, void* copy32,
+                         hipStream_t st, dd_dtype bt) {
+  if (passes == 1 && gs_step_fused(count, j + 1, a.m)) {
+    // beta is free between the normalisation of v_0 and the next cycle: it holds the step's activity flags
+    launch_gs_step(bt, vt, nrhs, count, ld, V, j, vstride, w, ws->partial, a.m, a.h1, a.H, a.cs, a.sn, a.gv, a.tolabs,
+                   a.active, reinterpret_cast<int*>(a.beta), a.kcyc, a.est, a.hnext, next, copy32, st);
+    return;
+  }
+  cgs(ws, a, vt, nrhs, count, ld, V, vstride, j + 1, w, passes, st, bt);
+  launch_arnoldi(nrhs, a.m, j, a.h1, passes == 2 ? a.h2 : nullptr, a.nrm2, a.H, a.cs, a.sn, a.gv, a.tolabs, a.active,
+                 a.kcyc, a.est, a.hnext, st);
+  if (next) launch_normalize(vt, nrhs, count, ld, w, nullptr, a.hnext, a.active, next, st, bt, copy32);
 }
 
 // ---------------------------------------------------------------------------
@@ -355,12 +382,9 @@ static void issue_chunk(const CoarseOps& c, Workspace* w, Arnoldi& a, int passes
   const bool half = c.basis == DD_F16;   // the operator then reads v_j from its FP32 copy (w->cv32)
   for (int j = j0; j < j0 + len; ++j) {
     schur_apply(c, nrhs, half ? w->cv32 : CV + (size_t)j * vs * c.bb, w->cw, w->ct1, w->ct2, st);
-    cgs(w, a, c.vt, nrhs, ce, ld, CV, vs, j + 1, w->cw, passes, st, c.basis);
-    launch_arnoldi(nrhs, a.m, j, a.h1, passes == 2 ? a.h2 : nullptr, a.nrm2, a.H, a.cs, a.sn, a.gv, a.tolabs,
-                   a.active, a.kcyc, a.est, a.hnext, st);
-    if (ends && j + 1 == j0 + len) break;
-    launch_normalize(c.vt, nrhs, ce, ld, w->cw, nullptr, a.hnext, a.active, CV + (size_t)(j + 1) * vs * c.bb, st,
-                     c.basis, half ? w->cv32 : nullptr);
+    const bool last = ends && j + 1 == j0 + len;
+    arnoldi_step(w, a, c.vt, nrhs, ce, ld, CV, vs, j, w->cw, passes,
+                 last ? nullptr : CV + (size_t)(j + 1) * vs * c.bb, half && !last ? w->cv32 : nullptr, st, c.basis);
   }
 }
 
@@ -448,19 +472,9 @@ static dd_status coarse_solve_ops(dd_ctx* ctx, Workspace* w, bool graphs, const 
   launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 1, nrhs, g.Vch, g.Vch, 1.0, b, 0.0, nullptr, 0.0, nullptr, w->ct1, st, c.spw, c.bt, c.hm);
   launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 0, nrhs, 0, g.Vch, 0.0, nullptr, -1.0, w->ct1, 1.0, b, w->cr, st, c.spw, c.bt, c.hm);
   DD_HIP(ctx, hipMemsetAsync(y, 0, (size_t)nrhs * ld * vb, st));
-  // tolerance: tol * |rhs'|
+  // tolerance tol * |rhs'|, no right-hand side finished yet
   norms2(w, vt, nrhs, ce, ld, w->cr, a.nrm2, st);
-  {
-    HostArr<double2> n2(nrhs);
-    HostArr<double> tl(nrhs);
-    HostArr<int> fin(nrhs, 0);
-    DD_HIP(ctx, hipMemcpyAsync(n2.p, a.nrm2, sizeof(double2) * nrhs, hipMemcpyDeviceToHost, st));
-    DD_HIP(ctx, hipStreamSynchronize(st));
-    for (int r = 0; r < nrhs; ++r) tl[r] = tol * std::sqrt(n2[r].x);
-    DD_HIP(ctx, hipMemcpyAsync(a.tolabs, tl.p, sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-    DD_HIP(ctx, hipMemcpyAsync(a.finished, fin.p, sizeof(int) * nrhs, hipMemcpyHostToDevice, st));
-    DD_HIP(ctx, hipStreamSynchronize(st));
-  }
+  launch_set_tol(nrhs, tol, a.nrm2, a.tolabs, a.finished, a.active, st);
   const long long vs = (long long)nrhs * ld;   // basis stride
   char* CV = (char*)w->CV;
   if (w->cv_type != c.basis) {
@@ -469,17 +483,17 @@ static dd_status coarse_solve_ops(dd_ctx* ctx, Workspace* w, bool graphs, const 
   }
   int iters = 0;
   while (iters < cap) {
-    // r = rhs' - S y  (first cycle: y = 0)
-    if (iters == 0) {
-      DD_HIP(ctx, hipMemcpyAsync(w->cres, w->cr, (size_t)nrhs * ld * vb, hipMemcpyDeviceToDevice, st));
-    } else {
+    // r = rhs' - S y; in the first cycle y = 0, so r and its norm are there
+    const void* res = w->cr;
+    if (iters > 0) {
+      res = w->cres;
       schur_apply(c, nrhs, y, w->cw, w->ct1, w->ct2, st);
       launch_sub(vt, (long long)nrhs * ld, w->cr, w->cw, w->cres, st);
+      norms2(w, vt, nrhs, ce, ld, w->cres, a.nrm2, st);
     }
-    norms2(w, vt, nrhs, ce, ld, w->cres, a.nrm2, st);
     launch_cycle_init(nrhs, m, a.nrm2, a.tolabs, a.finished, a.gv, a.beta, a.active, a.kcyc, st);
-    if (count_active(w, a.active, nrhs, st) == 0) break;
-    launch_normalize(vt, nrhs, ce, ld, w->cres, nullptr, a.beta, a.active, CV, st, c.basis,
+    if (fetch_status(w, a, nrhs, st) == 0) break;
+    launch_normalize(vt, nrhs, ce, ld, res, nullptr, a.beta, a.active, CV, st, c.basis,
                      c.basis == DD_F16 ? w->cv32 : nullptr);
     const int mm = (cap - iters < m) ? cap - iters : m;
     // chunks of 4 Arnoldi steps; converged RHS are masked on the device and the
@@ -491,22 +505,20 @@ static dd_status coarse_solve_ops(dd_ctx* ctx, Workspace* w, bool graphs, const 
       if (cs) return cs;
       iters += len;
       j += len;
-      if (ends || count_active(w, a.active, nrhs, st) == 0) break;
+      if (fetch_status(w, a, nrhs, st) == 0 || ends) break;
     }
     launch_lsq(nrhs, m, a.H, a.gv, a.kcyc, a.y, st);
-    launch_multi_axpy(c.basis, vt, nrhs, ce, ld, CV, max_kcyc(w, a, nrhs, st), vs, a.y, m, 0, 1.0, y, st);
+    launch_multi_axpy(c.basis, vt, nrhs, ce, ld, CV, longest_cycle(w, a, nrhs), vs, a.y, m, 0, 1.0, y, st);
     // RHS whose estimate met the tolerance are finished
-    DD_HIP(ctx, hipMemcpyAsync(w->hvals, a.est, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-    DD_HIP(ctx, hipMemcpyAsync(w->hvals + nrhs, a.tolabs, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-    DD_HIP(ctx, hipMemcpyAsync(w->hflags, a.finished, sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
-    DD_HIP(ctx, hipStreamSynchronize(st));
+    const double *est = a.in_status(w->hstat, a.est), *tolabs = a.in_status(w->hstat, a.tolabs);
+    int* fin = const_cast<int*>(a.in_status(w->hstat, a.finished));
     int nfin = 0;
     for (int r = 0; r < nrhs; ++r) {
-      if (w->hvals[r] <= w->hvals[nrhs + r]) w->hflags[r] = 1;
-      nfin += w->hflags[r];
+      if (est[r] <= tolabs[r]) fin[r] = 1;
+      nfin += fin[r];
     }
-    DD_HIP(ctx, hipMemcpyAsync(a.finished, w->hflags, sizeof(int) * nrhs, hipMemcpyHostToDevice, st));
     if (nfin == nrhs) break;
+    DD_HIP(ctx, hipMemcpyAsync(a.finished, fin, sizeof(int) * nrhs, hipMemcpyHostToDevice, st));
   }
   // odd sites: y_o = D_oo^-1 (b_o - D_oe y_e)
   odd_solve(c, nrhs, -1.0, y, 1.0, b, w->ct1, y, st);
@@ -691,21 +703,11 @@ static dd_status kcycle_solve(dd_mg* mg, dd_dtype vt, int nrhs, const void* b, v
   const double tol = L->p.kcycle_fixed ? 0.0 : L->p.kcycle_tol;
   char *V = (char*)w->CV, *Z = (char*)w->Z;
   norms2(w, vt, nrhs, ld, ld, b, a.nrm2, st);
-  {
-    HostArr<double2> n2(nrhs);
-    HostArr<double> tl(nrhs);
-    HostArr<int> fin(nrhs, 0);
-    DD_HIP(mg->ctx, hipMemcpyAsync(n2.p, a.nrm2, sizeof(double2) * nrhs, hipMemcpyDeviceToHost, st));
-    DD_HIP(mg->ctx, hipStreamSynchronize(st));
-    for (int r = 0; r < nrhs; ++r) tl[r] = tol * std::sqrt(n2[r].x);
-    DD_HIP(mg->ctx, hipMemcpyAsync(a.tolabs, tl.p, sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-    DD_HIP(mg->ctx, hipMemcpyAsync(a.finished, fin.p, sizeof(int) * nrhs, hipMemcpyHostToDevice, st));
-    DD_HIP(mg->ctx, hipStreamSynchronize(st));
-  }
+  launch_set_tol(nrhs, tol, a.nrm2, a.tolabs, a.finished, a.active, st);
   launch_cycle_init(nrhs, m, a.nrm2, a.tolabs, a.finished, a.gv, a.beta, a.active, a.kcyc, st);
   launch_zero(y, (size_t)nrhs * ld * vb, st);
   int steps = 0, total3 = 0;
-  if (count_active(w, a.active, nrhs, st) > 0) {
+  if (fetch_status(w, a, nrhs, st) > 0) {
     launch_normalize(vt, nrhs, ld, ld, b, nullptr, a.beta, a.active, V, st, vt);
     for (int j = 0; j < m; ++j) {
       char* Vj = V + (size_t)j * vs * vb;
@@ -720,16 +722,13 @@ static dd_status kcycle_solve(dd_mg* mg, dd_dtype vt, int nrhs, const void* b, v
       else
         launch_coarse_mv(g, vt, nc, c.Dc, c.Dinv, 0, nrhs, 0, g.Vc, 1.0, Zj, 1.0, Zj, 0.0, nullptr, w->cw, st, c.spw,
                          c.bt, c.hm);
-      cgs(w, a, vt, nrhs, ld, ld, V, vs, j + 1, w->cw, 1, st, vt);
-      launch_arnoldi(nrhs, m, j, a.h1, nullptr, a.nrm2, a.H, a.cs, a.sn, a.gv, a.tolabs, a.active, a.kcyc, a.est,
-                     a.hnext, st);
       steps = j + 1;
-      if (j + 1 == m) break;
-      launch_normalize(vt, nrhs, ld, ld, w->cw, nullptr, a.hnext, a.active, V + (size_t)(j + 1) * vs * vb, st, vt);
-      if (count_active(w, a.active, nrhs, st) == 0) break;
+      arnoldi_step(w, a, vt, nrhs, ld, ld, V, vs, j, w->cw, 1, j + 1 == m ? nullptr : V + (size_t)(j + 1) * vs * vb,
+                   nullptr, st, vt);
+      if (fetch_status(w, a, nrhs, st) == 0) break;
     }
     launch_lsq(nrhs, m, a.H, a.gv, a.kcyc, a.y, st);
-    launch_multi_axpy(vt, vt, nrhs, ld, ld, Z, max_kcyc(w, a, nrhs, st), vs, a.y, m, 0, 1.0, y, st);
+    launch_multi_axpy(vt, vt, nrhs, ld, ld, Z, longest_cycle(w, a, nrhs), vs, a.y, m, 0, 1.0, y, st);
   }
   DD_HIP(mg->ctx, hipGetLastError());
   L->last_steps = steps;
@@ -1559,18 +1558,15 @@ dd_status dd_coarse_solve_noalloc(dd_mg* mg, dd_dtype dt, int nrhs, const void* 
   w.arena.used = 0;
   carve_ws(w, sh, nrhs, false, false);
   // host mirrors of the per-RHS flags on the stack (no pinned allocation)
-  int hflags[2 * kHostRhs];
-  double hvals[3 * kHostRhs];
-  w.hflags = hflags;
-  w.hvals = hvals;
+  alignas(8) char hstat[status_capacity(kHostRhs)];
+  w.hstat = hstat;
   const hipStream_t st = (hipStream_t)stream;
   // the array keeps the last call's contents: start from zeros (finite basis entries)
   launch_zero(w.arena.base, bytes, st);
   w.cv_type = coarse_ops(mg, dt).basis;
   s = coarse_solve(mg, &w, false, dt, nrhs, in, out, iters, st);
   const hipError_t e = hipStreamSynchronize(st);   // the host mirrors live in this frame
-  w.hflags = nullptr;
-  w.hvals = nullptr;
+  w.hstat = nullptr;
   if (s) return s;
   if (e != hipSuccess) return dd_hip_check(mg->ctx, e, "allocation-free coarse solve");
   return DD_OK;
@@ -1880,14 +1876,12 @@ static dd_status solve_add(dd_solve_state* S, int slot, const double* b_canon) {
   DD_HIP(mg->ctx, hipMemsetAsync(w->x64 + (size_t)slot * cnt, 0, sizeof(double2) * cnt, st));
   DD_HIP(mg->ctx, hipMemcpyAsync(rs, bs, sizeof(double2) * cnt, hipMemcpyDeviceToDevice, st));
   norms2(w, DD_F64, 1, cnt, cnt, rs, w->fa.nrm2 + slot, st);
+  launch_set_tol(1, S->tol, w->fa.nrm2 + slot, w->fa.tolabs + slot, w->fa.finished + slot, w->fa.active + slot, st);
   double2 n2;
   DD_HIP(mg->ctx, hipMemcpyAsync(&n2, w->fa.nrm2 + slot, sizeof(double2), hipMemcpyDeviceToHost, st));
   DD_HIP(mg->ctx, hipStreamSynchronize(st));
   const double bn = std::sqrt(n2.x);
   if (!std::isfinite(bn)) return dd_fail(mg->ctx, DD_ENAN, "non-finite right-hand side in slot " + std::to_string(slot));
-  const double tl = S->tol * bn;
-  DD_HIP(mg->ctx, hipMemcpyAsync(w->fa.tolabs + slot, &tl, sizeof(double), hipMemcpyHostToDevice, st));
-  DD_HIP(mg->ctx, hipStreamSynchronize(st));
   S->bnorm[slot] = bn;
   S->relres[slot] = bn == 0.0 ? 0.0 : 1.0;
   S->iters[slot] = S->restarts[slot] = 0;
@@ -1944,20 +1938,17 @@ static dd_status solve_step(dd_solve_state* S) {
     }
     S->total_coarse += ci;
     const int op = mg->p.outer_cgs_passes;
-    cgs(w, a, DD_F64, nhi, cnt, cnt, w->V64, vs64, j + 1, w->w64, op, st, DD_F64);
-    launch_arnoldi(nhi, m, j, a.h1, op == 2 ? a.h2 : nullptr, a.nrm2, a.H, a.cs, a.sn, a.gv, a.tolabs, a.active,
-                   a.kcyc, a.est, a.hnext, st);
-    if (j + 1 == mm) break;
-    launch_normalize(DD_F64, nhi, cnt, cnt, w->w64, nullptr, a.hnext, a.active, w->V64 + (size_t)(j + 1) * vs64, st,
-                     DD_F64, vin32);
-    if (count_active(w, a.active, nhi, st) == 0) break;
+    arnoldi_step(w, a, DD_F64, nhi, cnt, cnt, w->V64, vs64, j, w->w64, op,
+                 j + 1 == mm ? nullptr : w->V64 + (size_t)(j + 1) * vs64, vin32, st, DD_F64);
+    if (fetch_status(w, a, nhi, st) == 0) break;
   }
   launch_lsq(nhi, m, a.H, a.gv, a.kcyc, a.y, st);
-  const int kmax = max_kcyc(w, a, nhi, st);   // also leaves kcyc in hflags[nhi..]
+  const int kmax = longest_cycle(w, a, nhi);
+  const int* kcyc = a.in_status(w->hstat, a.kcyc);
   launch_multi_axpy(vt, DD_F64, nhi, cnt, cnt, w->Z, kmax, vsz, a.y, m, 0, 1.0, w->x64, st);
   for (int r = 0; r < nhi; ++r)
     if (!fin[r]) {
-      S->iters[r] += w->hflags[nhi + r];
+      S->iters[r] += kcyc[r];
       S->restarts[r] += 1;
     }
   // true residual r = b - D x with the FP64 operator

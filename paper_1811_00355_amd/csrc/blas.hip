@@ -233,6 +233,9 @@ __global__ void __launch_bounds__(256) k_axpy_dots(int nrhs, long long count, lo
 // coarse lattices of small volumes, the level-3 lattice) EPT = 1, so that
 // they still spread over a few hundred workgroups.
 constexpr int kGsGroup = 4, kGsMaxNv = 128;
+// The step's reductions ride on its other launches up to this many tiles (64 at
+// 16^3x32, 2n = 40): 3 launches instead of 6.  Beyond it a workgroup would add up too many.
+constexpr int kGsFuseBlocks = 128;
 constexpr long long kGsShort = 1LL << 17;   // entries per right-hand side up to which EPT = 1
 
 // a[0..7] of every lane -> value (lane >> 3) summed over the wave (10 exchanges)
@@ -268,7 +271,7 @@ __device__ __forceinline__ double fold8(double* a, int lane) {
 // The loads of a group carry no conditions (indices are clamped into the
 // vectors and out-of-range terms are multiplied by zero), so a thread has all
 // EPT * kGsGroup of them in flight at once.
-template <typename Tv, typename Tw, int EPT>
+template <typename Tv, typename Tw, int EPT, bool FUSED>
 __global__ void __launch_bounds__(256) k_gs_dots(int nrhs, long long count, long long rs, const Tv* __restrict__ V,
                                                  int nv, long long vstride, const Tw* __restrict__ w,
                                                  double* __restrict__ partial, int nblk, Gate gt) {
@@ -310,24 +313,67 @@ __global__ void __launch_bounds__(256) k_gs_dots(int nrhs, long long count, long
     if ((lane & 7) == 0 && t < 2 * nv) red[wv][t] = s;
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < 2 * nv; t += blockDim.x)
-    partial[(((long long)r * nv + (t >> 1)) * nblk + blk) * 2 + (t & 1)] = red[0][t] + red[1][t] + red[2][t] + red[3][t];
+  // FUSED: [r][tile][2 nv], a tile's sums contiguous, for the workgroups that add up all tiles themselves;
+  // otherwise as k_reduce reads them
+  for (int t = threadIdx.x; t < 2 * nv; t += blockDim.x) {
+    const double v = red[0][t] + red[1][t] + red[2][t] + red[3][t];
+    if constexpr (FUSED) partial[((long long)r * nblk + blk) * 2 * nv + t] = v;
+    else partial[(((long long)r * nv + (t >> 1)) * nblk + blk) * 2 + (t & 1)] = v;
+  }
 }
 
-// w[r] <- w[r] - sum_{i < nv} coef[r * ldc + i] V_i[r], partial sums of |w|^2 over the same tiles
-template <typename Tv, typename Tw, int EPT>
+// w[r] <- w[r] - sum_{i < nv} coef[r * ldc + i] V_i[r], partial sums of |w|^2 over the same tiles.
+// FUSED (step.active set): every workgroup adds up the tiles' inner products itself (in tile order, two halves;
+// the sums are a few tens of KB from L2, against one more launch), the first one of a right-hand side stores them
+// as coef and notes whether the right-hand side is active in this step.
+template <typename Tv, typename Tw, int EPT, bool FUSED>
 __global__ void __launch_bounds__(256) k_gs_axpy_norm(int nrhs, long long count, long long rs,
                                                       const Tv* __restrict__ V, int nv, long long vstride,
-                                                      const double2* __restrict__ coef, int ldc, Tw* __restrict__ w,
-                                                      double* __restrict__ partial, int nblk, Gate gt) {
-  if (gate_closed(gt)) return;
+                                                      double2* __restrict__ coef, int ldc, Tw* __restrict__ w,
+                                                      const double* __restrict__ dots, double* __restrict__ partial,
+                                                      int nblk, const int* __restrict__ active,
+                                                      int* __restrict__ in_step, Gate gt) {
+  const bool closed = gate_closed(gt);
+  if constexpr (FUSED) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) in_step[blockIdx.y] = closed ? 0 : active[blockIdx.y];
+  }
+  if (closed) return;
   __shared__ cx<double> c[kGsMaxNv + kGsGroup];
   __shared__ double red[4];
+  __shared__ double half[FUSED ? 2 * kGsMaxNv : 1];
   const int r = blockIdx.y, blk = blockIdx.x, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nvp = (nv + kGsGroup - 1) / kGsGroup * kGsGroup;
-  for (int i = threadIdx.x; i < nvp; i += blockDim.x) {
-    const double2 v = i < nv ? coef[(long long)r * ldc + i] : make_double2(0.0, 0.0);   // padding: zero weight
-    c[i] = {v.x, v.y};
+  if constexpr (FUSED) {
+    // threads 0..127 and 128..255 take even and odd tiles
+    const int h = threadIdx.x >> 7, t0 = threadIdx.x & 127;
+    const double* d = dots + (long long)r * nblk * 2 * nv;
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int t = t0 + 128 * q;
+      if (t < 2 * nv) {
+#pragma unroll 8
+        for (int b = h; b < nblk; b += 2) s[q] += d[(long long)b * 2 * nv + t];
+        if (h == 1) half[t] = s[q];
+      }
+    }
+    __syncthreads();
+    if (h == 0) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int t = t0 + 128 * q;
+        if (t < 2 * nvp) {
+          const double v = t < 2 * nv ? s[q] + half[t] : 0.0;   // padding: zero weight
+          (t & 1 ? c[t >> 1].im : c[t >> 1].re) = v;
+          if (blk == 0 && t < 2 * nv) reinterpret_cast<double*>(coef + (long long)r * ldc)[t] = v;
+        }
+      }
+    }
+  } else {
+    for (int i = threadIdx.x; i < nvp; i += blockDim.x) {
+      const double2 v = i < nv ? coef[(long long)r * ldc + i] : make_double2(0.0, 0.0);   // padding: zero weight
+      c[i] = {v.x, v.y};
+    }
   }
   __syncthreads();
   const long long e0 = (long long)blk * (256 * EPT) + threadIdx.x;
@@ -368,9 +414,12 @@ __global__ void __launch_bounds__(256) k_gs_axpy_norm(int nrhs, long long count,
   n2 = wave_sum(n2);
   if (lane == 0) red[wv] = n2;
   __syncthreads();
-  if (threadIdx.x < 2)
-    partial[((long long)r * nblk + blk) * 2 + threadIdx.x] =
-        threadIdx.x == 0 ? red[0] + red[1] + red[2] + red[3] : 0.0;
+  const double n4 = red[0] + red[1] + red[2] + red[3];
+  if constexpr (FUSED) {
+    if (threadIdx.x == 0) partial[(long long)r * nblk + blk] = n4;
+  } else {
+    if (threadIdx.x < 2) partial[((long long)r * nblk + blk) * 2 + threadIdx.x] = threadIdx.x == 0 ? n4 : 0.0;
+  }
 }
 
 // dst[r] = src[r] / sqrt(nrm[r].x) where mask[r] != 0 (mask may be null); zero norm gives zero,
@@ -533,16 +582,13 @@ __device__ __forceinline__ cx<double> lane_get(cx<double> v, int i) {
   return {__shfl(v.re, i, 64), __shfl(v.im, i, 64)};
 }
 
-__global__ void __launch_bounds__(64) k_arnoldi_w(int m, int j, const double2* __restrict__ h1,
-                                                  const double2* __restrict__ h2, const double2* __restrict__ nrm2,
-                                                  double2* __restrict__ H, double* __restrict__ cs,
-                                                  double2* __restrict__ sn, double2* __restrict__ gv,
-                                                  const double* __restrict__ tolabs, int* __restrict__ active,
-                                                  int* __restrict__ kcyc, double* __restrict__ est,
-                                                  double* __restrict__ hnext, Gate gt) {
-  if (gate_closed(gt)) return;
-  const int r = blockIdx.x, lane = threadIdx.x;
-  if (!active[r]) return;   // uniform per wave
+// one wave's part: column j of right-hand side r with subdiagonal entry hn
+__device__ __forceinline__ void arnoldi_column(int r, int lane, int m, int j, const double2* __restrict__ h1,
+                                               const double2* __restrict__ h2, double hn, double2* __restrict__ H,
+                                               double* __restrict__ cs, double2* __restrict__ sn,
+                                               double2* __restrict__ gv, const double* __restrict__ tolabs,
+                                               int* __restrict__ active, int* __restrict__ kcyc,
+                                               double* __restrict__ est, double* __restrict__ hnext) {
   double2* Hc = H + ((long long)r * m + j) * (m + 1);   // column j
   cx<double> hc = {0.0, 0.0}, sl = {0.0, 0.0};
   double cl = 1.0;
@@ -555,7 +601,6 @@ __global__ void __launch_bounds__(64) k_arnoldi_w(int m, int j, const double2* _
     const double2 v = sn[r * m + lane];
     sl = {v.x, v.y};
   }
-  const double hn = sqrt(nrm2[r].x);
   // previous rotations, in order: (H_i, H_{i+1}) <- (c H_i + s H_{i+1}, c H_{i+1} - conj(s) H_i)
   cx<double> carry = lane_get(hc, 0), res = hc;
   for (int i = 0; i < j; ++i) {
@@ -599,6 +644,63 @@ __global__ void __launch_bounds__(64) k_arnoldi_w(int m, int j, const double2* _
     est[r] = e;
     kcyc[r] = j + 1;
     if (e <= tolabs[r] || hn == 0.0 || j + 1 == m) active[r] = 0;
+  }
+}
+
+__global__ void __launch_bounds__(64) k_arnoldi_w(int m, int j, const double2* __restrict__ h1,
+                                                  const double2* __restrict__ h2, const double2* __restrict__ nrm2,
+                                                  double2* __restrict__ H, double* __restrict__ cs,
+                                                  double2* __restrict__ sn, double2* __restrict__ gv,
+                                                  const double* __restrict__ tolabs, int* __restrict__ active,
+                                                  int* __restrict__ kcyc, double* __restrict__ est,
+                                                  double* __restrict__ hnext, Gate gt) {
+  if (gate_closed(gt)) return;
+  const int r = blockIdx.x;
+  if (!active[r]) return;   // uniform per wave
+  arnoldi_column(r, threadIdx.x, m, j, h1, h2, sqrt(nrm2[r].x), H, cs, sn, gv, tolabs, active, kcyc, est, hnext);
+}
+
+// End of a one-pass Arnoldi step in one launch (m <= 64): every wave adds up the
+// tiles' |w|^2 itself (nblk <= kGsFuseBlocks), the workgroups of a right-hand side
+// write dst = w / |w| (zeros when it was not active in this step), and an extra
+// one forms the Hessenberg column and its rotation.  A right-hand side that
+// converges in this step still gets its vector; the next step's are zeros again.
+template <typename Ts, typename Td>
+__global__ void __launch_bounds__(256) k_step_end(long long count, long long rs, const Ts* __restrict__ src,
+                                                  const double* __restrict__ partial, int nblk,
+                                                  const int* __restrict__ in_step, Td* __restrict__ dst,
+                                                  float2* __restrict__ copy32, int m, int j,
+                                                  const double2* __restrict__ h1, double2* __restrict__ H,
+                                                  double* __restrict__ cs, double2* __restrict__ sn,
+                                                  double2* __restrict__ gv, const double* __restrict__ tolabs,
+                                                  int* __restrict__ active, int* __restrict__ kcyc,
+                                                  double* __restrict__ est, double* __restrict__ hnext, Gate gt) {
+  if (gate_closed(gt)) return;
+  const int r = blockIdx.y, lane = threadIdx.x & 63;
+  double n2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < kGsFuseBlocks / 64; ++q) {
+    const int b = lane + 64 * q;
+    n2 += b < nblk ? partial[(long long)r * nblk + b] : 0.0;
+  }
+  const double n = sqrt(wave_sum(n2));
+  const bool on = in_step[r] != 0;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (on && threadIdx.x < 64)
+      arnoldi_column(r, lane, m, j, h1, nullptr, n, H, cs, sn, gv, tolabs, active, kcyc, est, hnext);
+    return;
+  }
+  const double s = n > 0.0 ? 1.0 / n : 0.0;
+  const long long step = (long long)(gridDim.x - 1) * blockDim.x;
+  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += step) {
+    const cx<double> v = on ? s * ld<double, Ts>(src + (long long)r * rs + e) : cx<double>{0.0, 0.0};
+    Td q;
+    st<Td, double>(&q, v);
+    dst[(long long)r * rs + e] = q;
+    if (copy32) {   // the stored (rounded) value, widened to FP32
+      const cx<float> f = ld<float, Td>(&q);
+      copy32[(long long)r * rs + e] = make_float2(f.re, f.im);
+    }
   }
 }
 
@@ -819,60 +921,88 @@ int gs_blocks(long long count) {
   return (int)((count + tile - 1) / tile);
 }
 
-// basis V of dtype bt (DD_F16 only with FP32 vectors), vector w of dtype vt, EPT entries per thread
-#define DD_GS_LAUNCH(KERNEL, EPT, ...)                                                                          \
-  if (vt == DD_F64)                                                                                             \
-    KERNEL<double2, double2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const double2*)V, nv, vstride,        \
-                                                        __VA_ARGS__, (double2*)w, partial, nblk, current_gate()); \
-  else if (bt == DD_F16)                                                                                        \
-    KERNEL<__half2, float2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const __half2*)V, nv, vstride,         \
-                                                       __VA_ARGS__, (float2*)w, partial, nblk, current_gate());  \
-  else                                                                                                          \
-    KERNEL<float2, float2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const float2*)V, nv, vstride,           \
-                                                      __VA_ARGS__, (float2*)w, partial, nblk, current_gate());
-#define DD_GS_DISPATCH(KERNEL, ...)            \
-  if (gs_ept(count) == 1) {                    \
-    DD_GS_LAUNCH(KERNEL, 1, __VA_ARGS__)       \
-  } else {                                     \
-    DD_GS_LAUNCH(KERNEL, 8, __VA_ARGS__)       \
+// basis V of dtype bt (DD_F16 only with FP32 vectors), vector w of dtype vt: BODY(Tv, Tw, EPT)
+#define DD_GS_TYPES(BODY)                                 \
+  if (vt == DD_F64) {                                     \
+    if (gs_ept(count) == 1) BODY(double2, double2, 1);    \
+    else BODY(double2, double2, 8);                       \
+  } else if (bt == DD_F16) {                              \
+    if (gs_ept(count) == 1) BODY(__half2, float2, 1);     \
+    else BODY(__half2, float2, 8);                        \
+  } else {                                                \
+    if (gs_ept(count) == 1) BODY(float2, float2, 1);      \
+    else BODY(float2, float2, 8);                         \
   }
+
+template <bool FUSED>
+static void gs_dots(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long rs, const void* V, int nv,
+                    long long vstride, const void* w, double* partial, hipStream_t st) {
+  const int nblk = gs_blocks(count);
+  const dim3 grid(nblk, nrhs);
+  const size_t es = vt == DD_F64 ? sizeof(double2) : sizeof(float2), eb = bt == DD_F16 ? 4 : es;
+  const double bytes = (double)nrhs * count * (nv * eb + es), flops = 8.0 * nrhs * count * nv;
+#define DD_GS_DOTS(TV, TW, EPT)                                                                              \
+  k_gs_dots<TV, TW, EPT, FUSED><<<grid, 256, 0, st>>>(nrhs, count, rs, (const TV*)V, nv, vstride, (const TW*)w, \
+                                                      partial, nblk, current_gate())
+  DD_TIMED("k_gs_dots", st, bytes, flops, DD_GS_TYPES(DD_GS_DOTS));
+#undef DD_GS_DOTS
+}
+
+template <bool FUSED>
+static void gs_axpy_norm(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long rs, const void* V, int nv,
+                         long long vstride, double2* coef, int ldc, void* w, const double* dots, double* partial,
+                         const int* active, int* in_step, hipStream_t st) {
+  const int nblk = gs_blocks(count);
+  const dim3 grid(nblk, nrhs);
+  const size_t es = vt == DD_F64 ? sizeof(double2) : sizeof(float2), eb = bt == DD_F16 ? 4 : es;
+  const double bytes = (double)nrhs * count * (nv * eb + 2 * es), flops = 8.0 * nrhs * count * (nv + 1);
+#define DD_GS_AXPY(TV, TW, EPT)                                                                                    \
+  k_gs_axpy_norm<TV, TW, EPT, FUSED><<<grid, 256, 0, st>>>(nrhs, count, rs, (const TV*)V, nv, vstride, coef, ldc,  \
+                                                           (TW*)w, dots, partial, nblk, active, in_step,           \
+                                                           current_gate())
+  DD_TIMED("k_gs_axpy_norm", st, bytes, flops, DD_GS_TYPES(DD_GS_AXPY));
+#undef DD_GS_AXPY
+}
+#undef DD_GS_TYPES
 
 void launch_gs_dots(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long rs, const void* V, int nv,
                     long long vstride, const void* w, double* partial, double2* out, int ldo, hipStream_t st) {
-  const int nblk = gs_blocks(count);
-  dim3 grid(nblk, nrhs);
-  const size_t es = vt == DD_F64 ? sizeof(double2) : sizeof(float2), eb = bt == DD_F16 ? 4 : es;
-  const double bytes = (double)nrhs * count * (nv * eb + es), flops = 8.0 * nrhs * count * nv;
-#define DD_GS_DOTS(EPT)                                                                                          \
-  if (vt == DD_F64)                                                                                              \
-    k_gs_dots<double2, double2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const double2*)V, nv, vstride,      \
-                                                           (const double2*)w, partial, nblk, current_gate());     \
-  else if (bt == DD_F16)                                                                                         \
-    k_gs_dots<__half2, float2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const __half2*)V, nv, vstride,       \
-                                                          (const float2*)w, partial, nblk, current_gate());       \
-  else                                                                                                           \
-    k_gs_dots<float2, float2, EPT><<<grid, 256, 0, st>>>(nrhs, count, rs, (const float2*)V, nv, vstride,         \
-                                                         (const float2*)w, partial, nblk, current_gate());
-  if (gs_ept(count) == 1)
-    DD_TIMED("k_gs_dots", st, bytes, flops, DD_GS_DOTS(1));
-  else
-    DD_TIMED("k_gs_dots", st, bytes, flops, DD_GS_DOTS(8));
-#undef DD_GS_DOTS
-  k_reduce<<<nrhs * nv, 256, 0, st>>>(nv, nblk, partial, out, ldo, 0, current_gate());
+  gs_dots<false>(bt, vt, nrhs, count, rs, V, nv, vstride, w, partial, st);
+  k_reduce<<<nrhs * nv, 256, 0, st>>>(nv, gs_blocks(count), partial, out, ldo, 0, current_gate());
 }
 
 void launch_gs_axpy_norm(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long rs, const void* V, int nv,
                          long long vstride, const double2* coef, int ldc, void* w, double* partial, double2* out,
                          hipStream_t st) {
-  const int nblk = gs_blocks(count);
-  dim3 grid(nblk, nrhs);
-  const size_t es = vt == DD_F64 ? sizeof(double2) : sizeof(float2), eb = bt == DD_F16 ? 4 : es;
-  const double bytes = (double)nrhs * count * (nv * eb + 2 * es), flops = 8.0 * nrhs * count * (nv + 1);
-  DD_TIMED("k_gs_axpy_norm", st, bytes, flops, DD_GS_DISPATCH(k_gs_axpy_norm, coef, ldc));
-  k_reduce<<<nrhs, 256, 0, st>>>(1, nblk, partial, out, 1, 0, current_gate());
+  gs_axpy_norm<false>(bt, vt, nrhs, count, rs, V, nv, vstride, const_cast<double2*>(coef), ldc, w, nullptr, partial,
+                      nullptr, nullptr, st);
+  k_reduce<<<nrhs, 256, 0, st>>>(1, gs_blocks(count), partial, out, 1, 0, current_gate());
 }
-#undef DD_GS_DISPATCH
-#undef DD_GS_LAUNCH
+
+// (nv < m: the tiles' norms then fit behind the inner products in the m-vector buffer of partial sums)
+bool gs_step_fused(long long count, int nv, int m) {
+  return nv < m && m <= 64 && gs_blocks(count) <= kGsFuseBlocks;
+}
+
+void launch_gs_step(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long rs, const void* V, int j,
+                    long long vstride, void* w, double* partial, int m, double2* h1, double2* H, double* cs,
+                    double2* sn, double2* gv, const double* tolabs, int* active, int* in_step, int* kcyc, double* est,
+                    double* hnext, void* dst, void* copy32, hipStream_t st) {
+  const int nv = j + 1, nblk = gs_blocks(count);
+  double* norms = partial + (size_t)nrhs * nblk * 2 * nv;   // past the inner products' partial sums
+  gs_dots<true>(bt, vt, nrhs, count, rs, V, nv, vstride, w, partial, st);
+  gs_axpy_norm<true>(bt, vt, nrhs, count, rs, V, nv, vstride, h1, m + 1, w, partial, norms, active, in_step, st);
+  Gate gt = current_gate();
+  if (gt.flags == active) gt.flags = in_step;   // the column's workgroup changes `active` while the others run
+  const dim3 grid((dst ? grid1(count) : 0) + 1, nrhs);
+#define DD_STEP_END(TS, TD)                                                                                        \
+  k_step_end<TS, TD><<<grid, 256, 0, st>>>(count, rs, (const TS*)w, norms, nblk, in_step, (TD*)dst, (float2*)copy32, m, \
+                                           j, h1, H, cs, sn, gv, tolabs, active, kcyc, est, hnext, gt)
+  if (vt == DD_F64) DD_STEP_END(double2, double2);
+  else if (bt == DD_F16) DD_STEP_END(float2, __half2);
+  else DD_STEP_END(float2, float2);
+#undef DD_STEP_END
+}
 
 void launch_normalize(dd_dtype vt, int nrhs, long long count, long long rs, const void* src, const double2* nrm2,
                       const double* nrm, const int* mask, void* dst, hipStream_t st, dd_dtype dt, void* copy32) {

@@ -491,6 +491,14 @@ void launch_gs_dots(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long lo
 void launch_gs_axpy_norm(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long ld, const void* V, int nv,
                          long long vstride, const double2* coef, int ldc, void* w, double* partial, double2* out,
                          hipStream_t st);
+// one-pass Arnoldi step j after w = A v_j in three launches, where gs_step_fused: h1 = V^dag w, w -= V h1, |w|, the
+// Hessenberg column with its rotation, and (dst set) v_{j+1} = w / |w| with an optional FP32 copy.  partial: 2 m
+// values per right-hand side and tile; in_step: nrhs flags
+bool gs_step_fused(long long count, int nv, int m);
+void launch_gs_step(dd_dtype bt, dd_dtype vt, int nrhs, long long count, long long ld, const void* V, int j,
+                    long long vstride, void* w, double* partial, int m, double2* h1, double2* H, double* cs,
+                    double2* sn, double2* gv, const double* tolabs, int* active, int* in_step, int* kcyc, double* est,
+                    double* hnext, void* dst, void* copy32, hipStream_t st);
 void launch_normalize(dd_dtype vt, int nrhs, long long count, long long ld, const void* src, const double2* nrm2,
                       const double* nrm, const int* mask, void* dst, hipStream_t st,
                       dd_dtype dt = DD_F32, void* copy32 = nullptr);   // dt: dtype of dst (F16 basis)
