@@ -935,10 +935,8 @@ static dd_status build(dd_mg* mg, hipStream_t st) {
   dd_status s;
   if ((s = dd_alloc(mg->ctx, (void**)&dflag, sizeof(int)))) return s;
   int neg = -1;
-  // P64 <- working vectors
-  launch_vec_convert(inner_vt(mg), DD_F64, mg->tv, mg->P64, nfine, st);
   DD_HIP(mg->ctx, hipMemcpyAsync(dflag, &neg, sizeof(int), hipMemcpyHostToDevice, st));
-  launch_gram_schmidt(G, mg->n, mg->P64, dflag, st);
+  launch_gram_schmidt(G, inner_vt(mg), mg->n, mg->tv, mg->P64, dflag, st);
   int bad = -1;
   DD_HIP(mg->ctx, hipMemcpyAsync(&bad, dflag, sizeof(int), hipMemcpyDeviceToHost, st));
   DD_HIP(mg->ctx, hipStreamSynchronize(st));
@@ -948,28 +946,8 @@ static dd_status build(dd_mg* mg, hipStream_t st) {
                    "test vectors are rank deficient on aggregate slot " + std::to_string(bad / 2) + " chirality " +
                        std::to_string(bad % 2));
   }
-  // stored copy of P: FP32 from FP64, half precision from the FP32 copy
-  if (mg->vstore != DD_F64) {
-    if (mg->vstore == DD_F32) {
-      launch_convert_pairs(DD_F32, mg->P64, nullptr, mg->Pst, nfine, st);
-    } else {
-      // through an FP32 staging buffer of at most 2^27 pairs (1 GiB), chunk by chunk
-      const long long cap = 1LL << 27, len = nfine < cap ? nfine : cap;
-      float2* stage = nullptr;
-      if ((s = dd_alloc(mg->ctx, (void**)&stage, sizeof(float2) * len))) {
-        dd_free(mg->ctx, dflag, sizeof(int));
-        return s;
-      }
-      const size_t pb = storage_pair_bytes(mg->vstore);
-      for (long long o = 0; o < nfine; o += len) {
-        const long long cnt = nfine - o < len ? nfine - o : len;
-        launch_convert_pairs(DD_F32, mg->P64 + o, nullptr, stage, cnt, st);
-        launch_convert_pairs(mg->vstore, nullptr, stage, (char*)mg->Pst + o * pb, cnt, st);
-      }
-      DD_HIP(mg->ctx, hipStreamSynchronize(st));
-      dd_free(mg->ctx, stage, sizeof(float2) * len);
-    }
-  }
+  // stored copy of P (half precision through an FP32 rounding)
+  if (mg->vstore != DD_F64) launch_convert_pairs(mg->vstore, mg->P64, nullptr, mg->Pst, nfine, st);
   // Galerkin operator from the stored P and the FP64 operator: directly for 4^4
   // aggregates, otherwise through FP64 fine vectors.  W holds `chunk` of those
   // (columns of D_c built per pass over P): as many as fit in
@@ -1425,7 +1403,9 @@ dd_status dd_footprint_bytes(const dd_problem* prob, const dd_mg_params* p, int 
                  (16 + 8) * blocks;
   if (st == DD_F16 || st == DD_BF16) setup += 4 * blocks;
   // scratch while a setup runs: the V-cycle workspace for the n vectors, the
-  // build's flag, then the FP32 staging of a half P or the Galerkin chunk
+  // build's flag, then the Galerkin chunk or, for a half P, the FP32 copy of up to
+  // 1 GiB that a caller's budget has always been asked to leave (neither is taken on
+  // 4^4 blocks)
   const WsShape sh{V, Vc, Vc / 2, (int)nc, p->coarse_restart, p->fgmres_restart, vt};
   const long long vbytes = 12 * V * (long long)sizeof(double2);
   long long chunk = std::min<long long>((long long)((4ULL << 30) / (size_t)vbytes), nc);

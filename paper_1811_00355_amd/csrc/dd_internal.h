@@ -449,7 +449,8 @@ void launch_restrict(const GeomDev& g, dd_dtype vt, dd_dtype pst, int n, const v
                      const void* fine, void* coarse, hipStream_t st);
 void launch_prolong(const GeomDev& g, dd_dtype vt, dd_dtype pst, int n, const void* P, int nrhs,
                     const void* coarse, void* fine, hipStream_t st);
-void launch_gram_schmidt(const GeomDev& g, int n, double2* P, int* bad_flag, hipStream_t st);
+void launch_gram_schmidt(const GeomDev& g, dd_dtype vt, int n, const void* in, double2* P, int* bad_flag,
+                         hipStream_t st);
 void launch_coarse_build(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P,
                          double2* Dc64, double2* W, int chunk, hipStream_t st);
 // the same without the scratch vectors, for 4^4 aggregates (galerkin_direct)

@@ -67,6 +67,25 @@ __global__ void k_f32_to_bf16(const float2* __restrict__ s, bf16x2* __restrict__
     d[i].u = lo | (hi << 16);
   }
 }
+// the same two roundings in one pass, for an FP64 array without an FP32 copy: the
+// float between them is made opaque
+__device__ __forceinline__ float2 round_f32(double2 v) {
+  float2 f = make_float2((float)v.x, (float)v.y);
+  asm volatile("" : "+v"(f.x), "+v"(f.y));
+  return f;
+}
+__global__ void k_f64_to_f16(const double2* __restrict__ s, __half2* __restrict__ d, long long n) {
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float2 f = round_f32(s[i]);
+  d[i] = __floats2half2_rn(f.x, f.y);
+}
+__global__ void k_f64_to_bf16(const double2* __restrict__ s, bf16x2* __restrict__ d, long long n) {
+  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float2 f = round_f32(s[i]);
+  d[i].u = f32_to_bf16_bits(f.x) | (f32_to_bf16_bits(f.y) << 16);
+}
 __global__ void k_copy2(const double2* __restrict__ s, double2* __restrict__ d, long long n) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) d[i] = s[i];
@@ -113,8 +132,14 @@ void launch_convert_pairs(dd_dtype to, const double2* src64, const float2* src32
   switch (to) {
     case DD_F64: k_copy2<<<nb, 256, 0, st>>>(src64, (double2*)dst, n); break;
     case DD_F32: k_to_f32<<<nb, 256, 0, st>>>(src64, (float2*)dst, n); break;
-    case DD_F16: k_f32_to_f16<<<nb, 256, 0, st>>>(src32, (__half2*)dst, n); break;
-    case DD_BF16: k_f32_to_bf16<<<nb, 256, 0, st>>>(src32, (bf16x2*)dst, n); break;
+    case DD_F16:
+      if (src32) k_f32_to_f16<<<nb, 256, 0, st>>>(src32, (__half2*)dst, n);
+      else k_f64_to_f16<<<nb, 256, 0, st>>>(src64, (__half2*)dst, n);
+      break;
+    case DD_BF16:
+      if (src32) k_f32_to_bf16<<<nb, 256, 0, st>>>(src32, (bf16x2*)dst, n);
+      else k_f64_to_bf16<<<nb, 256, 0, st>>>(src64, (bf16x2*)dst, n);
+      break;
   }
 }
 

@@ -308,69 +308,186 @@ __global__ void __launch_bounds__(256) k_prolong(GeomDev g, int n, const Sp* __r
 }
 
 // ---------------------------------------------------------------------------
-// two-pass modified Gram-Schmidt per (aggregate, chirality), FP64, in place
+// Gram-Schmidt per (aggregate, chirality), FP64: P = the orthonormalised test
+// vectors, read in their working type.
+//
+// B vectors at a time live in registers (two threads per site, three components
+// each): they are made orthogonal to the finished vectors, then to one another,
+// and both are done a second time on the normalised vectors, so that every vector
+// sees every other twice.  Bound by the re-reading of the finished vectors (one
+// vector at a time n^2 reads of a vector, B at a time about n^2 / B) and by the
+// reductions between them: the sums of B vectors and two finished ones are reduced
+// together (halving exchanges in a wave, one LDS word per wave and sum, one barrier)
+// and come back in scalar registers.  16^3x32, n = 20: 1730 us one vector and one
+// sum at a time; B = 8 (one workgroup per CU) 976, B = 4 (two) 649, B = 4 with two
+// finished vectors to a reduction 607 (2.8 GB, 4.6 TB/s).  Reading the working type
+// here also saves its FP64 copy (117 us).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void block_sum2(double& a, double& b, double* red) {
-  a = wave_sum(a);
-  b = wave_sum(b);
-  int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (blockDim.x + 63) >> 6;
-  __syncthreads();
-  if (lane == 0) {
-    red[2 * w] = a;
-    red[2 * w + 1] = b;
-  }
-  __syncthreads();
-  a = b = 0.0;
-  for (int q = 0; q < nw; ++q) {
-    a += red[2 * q];
-    b += red[2 * q + 1];
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// halving exchange: lanes with `up` keep the upper W sums, the others the lower W
+template <int W, int CTRL>
+__device__ __forceinline__ void halve(double* a, bool up) {
+#pragma unroll
+  for (int k = 0; k < W; ++k) {
+    const double send = up ? a[k] : a[k + W], keep = up ? a[k + W] : a[k];
+    a[k] = keep + dpp_f64<CTRL>(send);
   }
 }
 
-__global__ void __launch_bounds__(256) k_gram_schmidt(GeomDev g, int n, double2* __restrict__ P, int* bad) {
-  __shared__ double red[16];
+// sums over the workgroup of the B complex numbers d, the same in every lane.  red:
+// this step's half of a double buffer, [waves][2 B]
+template <int B>
+__device__ __forceinline__ void block_sums(cx<double>* d, double* red) {
+  static_assert(B == 8 || B == 4, "");
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  double a[2 * B];
+#pragma unroll
+  for (int k = 0; k < B; ++k) {
+    a[2 * k] = d[k].re;
+    a[2 * k + 1] = d[k].im;
+  }
+  // partners: lane ^ 15, ^ 7, ^ 2, ^ 1 (row mirror, half mirror, quad permutes)
+  int idx;
+  if constexpr (B == 8) {
+    halve<8, 0x140>(a, lane & 8);
+    halve<4, 0x141>(a, lane & 4);
+    halve<2, 0x4E>(a, lane & 2);
+    halve<1, 0xB1>(a, lane & 1);
+    idx = lane & 15;
+  } else {
+    halve<4, 0x140>(a, lane & 8);
+    halve<2, 0x141>(a, lane & 4);
+    halve<1, 0x4E>(a, lane & 2);
+    a[0] += dpp_f64<0xB1>(a[0]);
+    idx = (lane & 15) >> 1;
+  }
+  a[0] += __shfl_xor(a[0], 16, 64);
+  a[0] += __shfl_xor(a[0], 32, 64);
+  if (lane < 16) red[w * 2 * B + idx] = a[0];
+  __syncthreads();
+  double t = 0.0;
+  for (int q = 0; q < nw; ++q) t += red[q * 2 * B + idx];
+#pragma unroll
+  for (int k = 0; k < B; ++k) d[k] = {lane_f64(t, B == 8 ? 2 * k : 4 * k), lane_f64(t, B == 8 ? 2 * k + 1 : 4 * k + 2)};
+}
+
+// acc += conj(a) b and acc -= a b in four fused operations each
+__device__ __forceinline__ void dot_fma(cx<double>& acc, cx<double> a, cx<double> b) {
+  acc.re = __builtin_fma(a.im, b.im, __builtin_fma(a.re, b.re, acc.re));
+  acc.im = __builtin_fma(-a.im, b.re, __builtin_fma(a.re, b.im, acc.im));
+}
+__device__ __forceinline__ void sub_fma(cx<double>& acc, cx<double> a, cx<double> b) {
+  acc.re = __builtin_fma(a.im, b.im, __builtin_fma(-a.re, b.re, acc.re));
+  acc.im = __builtin_fma(-a.im, b.re, __builtin_fma(-a.re, b.im, acc.im));
+}
+
+template <int B, typename Tin>
+__global__ void __launch_bounds__(512) k_gram_schmidt(GeomDev g, int n, const Tin* __restrict__ in, double2* P, int* bad) {
+  __shared__ double red[2][8 * 4 * B];
   const int slot = blockIdx.x >> 1, s = blockIdx.x & 1;
-  const int j = threadIdx.x;
-  const bool act = j < g.Bv;
-  const long long V = g.V;
-  const long long I = ((long long)slot << g.lBv) + (act ? j : 0);
-  for (int i = 0; i < n; ++i) {
-    cx<double> v[6];
-    double2* vi = P + (long long)i * 12 * V + (long long)(6 * s) * V + I;
+  const int h = threadIdx.x >> g.lBv, j = threadIdx.x & (g.Bv - 1);
+  const bool act = h < 2;
+  const long long V = g.V, nv = 12 * V;
+  const long long o = (long long)(6 * s + (act ? 3 * h : 0)) * V + ((long long)slot << g.lBv) + j;
+  int turn = 0;
+  for (int i0 = 0; i0 < n; i0 += B) {
+    const int nb = n - i0 < B ? n - i0 : B;
+    cx<double> v[B][3], d[B];
+    double n0[B];   // squared norms before anything is taken out
 #pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] = act ? ld<double, double2>(vi + c * V) : cx<double>{0.0, 0.0};
-    double n0 = 0.0;
+    for (int b = 0; b < B; ++b) {
+      d[b] = {0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < 6; ++c) n0 += v[c].re * v[c].re + v[c].im * v[c].im;
-    double dummy = 0.0;
-    block_sum2(n0, dummy, red);
-    for (int pass = 0; pass < 2; ++pass)
-      for (int q = 0; q < i; ++q) {
-        const double2* vq = P + (long long)q * 12 * V + (long long)(6 * s) * V + I;
-        cx<double> u[6];
-        cx<double> dt = {0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-          u[c] = act ? ld<double, double2>(vq + c * V) : cx<double>{0.0, 0.0};
-          cfma_conj(dt, u[c], v[c]);
-        }
-        block_sum2(dt.re, dt.im, red);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) v[c] = v[c] - dt * u[c];
+      for (int c = 0; c < 3; ++c) {
+        v[b][c] = act && b < nb ? ld<double, Tin>(in + (i0 + b) * nv + o + c * V) : cx<double>{0.0, 0.0};
+        d[b].re += v[b][c].re * v[b][c].re + v[b][c].im * v[b][c].im;
       }
-    double nn = 0.0;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) nn += v[c].re * v[c].re + v[c].im * v[c].im;
-    block_sum2(nn, dummy, red);
-    double nrm = sqrt(nn);
-    if (nrm <= 1e-12 * sqrt(n0)) {
-      if (threadIdx.x == 0) atomicCAS(bad, -1, 2 * slot + s);
-      nrm = 1.0;
     }
-    double inv = 1.0 / nrm;
+    block_sums<B>(d, red[turn]);
+    turn ^= 1;
+#pragma unroll
+    for (int b = 0; b < B; ++b) n0[b] = d[b].re;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+      // out of the finished vectors' span, two of them at a time
+#pragma unroll 1
+      for (int q = 0; q < i0; q += 2) {
+        cx<double> u[2][3], e[2 * B];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            u[p][c] = act ? ld<double, double2>(P + (q + p) * nv + o + c * V) : cx<double>{0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < 2 * B; ++b) {
+          e[b] = {0.0, 0.0};
+#pragma unroll
+          for (int c = 0; c < 3; ++c) dot_fma(e[b], u[b / B][c], v[b % B][c]);
+        }
+        block_sums<2 * B>(e, red[turn]);
+        turn ^= 1;
+#pragma unroll
+        for (int b = 0; b < 2 * B; ++b)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) sub_fma(v[b % B][c], e[b], u[b / B][c]);
+      }
+      // out of one another: the front vector is normalised, taken out of those
+      // after it and moved to the back; B steps restore the order
+#pragma unroll 1
+      for (int i = 0; i < B; ++i) {
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+          d[b] = {0.0, 0.0};
+#pragma unroll
+          for (int c = 0; c < 3; ++c) dot_fma(d[b], v[0][c], v[b][c]);
+        }
+        block_sums<B>(d, red[turn]);
+        turn ^= 1;
+        double nrm = sqrt(d[0].re);
+        if (pass == 0 && i < nb && nrm <= 1e-12 * sqrt(n0[0])) {
+          if (threadIdx.x == 0) atomicCAS(bad, -1, 2 * slot + s);
+          nrm = 1.0;
+        }
+        const double inv = nrm == 0.0 ? 1.0 : 1.0 / nrm;
+        cx<double> f[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) f[c] = inv * v[0][c];
+        const double nf = n0[0];
+#pragma unroll
+        for (int b = 1; b < B; ++b) {
+          if (b < nb - i) {
+            const cx<double> t = inv * d[b];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sub_fma(v[b][c], t, f[c]);
+          }
+#pragma unroll
+          for (int c = 0; c < 3; ++c) v[b - 1][c] = v[b][c];
+          n0[b - 1] = n0[b];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[B - 1][c] = f[c];
+        n0[B - 1] = nf;
+      }
+    }
     if (act)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) st<double2, double>(vi + c * V, inv * v[c]);
+      for (int b = 0; b < B; ++b)
+        if (b < nb)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) st<double2, double>(P + (i0 + b) * nv + o + c * V, v[b][c]);
   }
 }
 
@@ -649,9 +766,11 @@ void launch_prolong(const GeomDev& g, dd_dtype vt, dd_dtype pst, int n, const vo
   DD_TIMED("k_prolong", st, bytes, flops, prolong_dispatch(g, vt, pst, n, P, nrhs, coarse, fine, st));
 }
 
-void launch_gram_schmidt(const GeomDev& g, int n, double2* P, int* bad_flag, hipStream_t st) {
-  int threads = g.Bv < 64 ? 64 : g.Bv;
-  k_gram_schmidt<<<(unsigned)g.Vc * 2, threads, 0, st>>>(g, n, P, bad_flag);
+void launch_gram_schmidt(const GeomDev& g, dd_dtype vt, int n, const void* in, double2* P, int* bad_flag, hipStream_t st) {
+  const int threads = 2 * g.Bv < 64 ? 64 : 2 * g.Bv;
+  const unsigned nb = (unsigned)g.Vc * 2;
+  if (vt == DD_F64) k_gram_schmidt<4, double2><<<nb, threads, 0, st>>>(g, n, (const double2*)in, P, bad_flag);
+  else k_gram_schmidt<4, float2><<<nb, threads, 0, st>>>(g, n, (const float2*)in, P, bad_flag);
 }
 
 // D_c = P^dag D P in FP64 from the stored test vectors (pst) and the FP64 operator.
