@@ -31,12 +31,14 @@ __global__ void __launch_bounds__(256) k_dirac(GeomDev g, const S* __restrict__ 
   store_spinor<R, To>(out + (long long)r * 12 * g.V, g.V, I, acc);
 }
 
-// With one right-hand side the streams read or written once per launch (the
-// clover operand, the output spinor) take non-temporal accesses, so that L2
-// keeps what neighbouring sites read again: the links (a site's forward link
-// is its backward neighbour's backward link) and the face spinors of
-// neighbouring blocks.  With several right-hand sides each RHS's workgroup
-// re-reads the clover, and L2 should keep it.
+// Streams that no other workgroup reads soon take non-temporal accesses, so that L2
+// keeps what is read again: the links (a site's forward link is its backward
+// neighbour's backward link), the spinors of x and y neighbours and, for the other
+// right-hand sides' workgroups, the operator.  The streams are the output, with one
+// right-hand side the clover operand, and with several z and t neighbours' spinors
+// where x and y ones are read ahead (FP64).  32^3x64, FP64, twelve right-hand sides: 6112
+// us without, 5950 with the output, 5862 with the neighbours as well; y neighbours
+// too 5820, but 4 % slower on 24^3x48; the own spinors too 7236.
 template <typename R, typename S>
 __device__ __forceinline__ cx<R> ld_stream(const S* p) {
   return ld<R, S>(p);
@@ -66,6 +68,12 @@ template <>
 __device__ __forceinline__ void st_stream<float2, float>(float2* p, cx<float> v) {
   typedef float v2 __attribute__((ext_vector_type(2)));
   __builtin_nontemporal_store(v2{v.re, v.im}, reinterpret_cast<v2*>(p));
+}
+
+template <typename R, typename Tv>
+__device__ __forceinline__ void load_spinor_stream(const Tv* p, long long V, long long I, cx<R>* psi) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) psi[c] = ld_stream<R, Tv>(p + (long long)c * V + I);
 }
 
 // C psi for the packed clover (two Hermitian 6x6 blocks), operand read as a stream
@@ -200,9 +208,9 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
 // spinor plus the faces.  NF (see blk_launch) is what leaves the CU its workgroups:
 // all eight faces in FP32 (48 KB), x and y in FP64 (72 KB; the z and t faces are whole
 // lines, and their blocks run far apart in the slab order).  Bound by traffic:
-// at 32^3x64, FP64, twelve right-hand sides, 32 GB a launch (2.7 times the algorithmic
-// bytes) at 5.3 TB/s; two right-hand sides of a block in one workgroup measured
-// slower (7.2 against 6.1 ms).
+// at 32^3x64, FP64, twelve right-hand sides, about 31 GB a launch (2.6 times the
+// algorithmic bytes) at 5.3 TB/s; two right-hand sides of a block in one workgroup
+// measured slower (7.2 against 6.1 ms).
 template <typename R, typename S, typename Tv, typename To, bool NT, int NF>
 __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restrict__ links,
                                                    const S* __restrict__ clov, int nrhs, const Tv* __restrict__ in,
@@ -235,17 +243,14 @@ __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restric
 #pragma unroll
       for (int c = 6; c < 12; ++c) p[c] = {(R)0, (R)0};
     } else {
-      load_spinor<R, Tv>(x, g.V, J, p);
+      if constexpr (!NT && NF == 4) load_spinor_stream<R, Tv>(x, g.V, J, p);   // z and t neighbours
+      else load_spinor<R, Tv>(x, g.V, J, p);
     }
   };
   hop_pairs<R, S>(g, links, s, I, fetch, acc);
   To* o = out + (long long)r * 12 * g.V;
-  if constexpr (NT) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) st_stream<To, R>(o + (long long)c * g.V + I, acc[c]);
-  } else {
-    store_spinor<R, To>(o, g.V, I, acc);
-  }
+  for (int c = 0; c < 12; ++c) st_stream<To, R>(o + (long long)c * g.V + I, acc[c]);
 }
 
 // Half-precision operands, several right-hand sides (4^4 blocks): one workgroup
@@ -360,13 +365,14 @@ constexpr double kDiracFlopsPerSite = 1320.0 + 504.0 + 24.0;
 
 }  // namespace
 
-// Block form.  With one right-hand side the clover and the output are streamed.
+// Block form.  With one right-hand side the clover is streamed.
 // Faces in LDS: x and y in FP64, all in FP32, none for half operands (their launch
 // moves half the bytes, and the halos gave nothing) and none on lattices of at
 // most 256 blocks, which run together anyway, so that the faces would be one more
 // latency.  (By the lattice and not by the launch: the two forms round differently,
 // and a right-hand side has the same bits in every batch.)  us, without / with faces:
-// FP64 32^3x64 one right-hand side 733 / 697, twelve 6522 / 6125; FP32 24^3x48 113 / 103,
+// FP64 32^3x64 one right-hand side 733 / 697, twelve 6522 / 6125 (5862 with streamed
+// outputs and far neighbours); FP32 24^3x48 113 / 103,
 // twelve 1148 / 1055; 8^4 FP32 13.1 / 14.1, FP64 14.1 / 15.8.
 template <typename R, typename S, typename Tv, typename To>
 void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, void* out, hipStream_t st) {
