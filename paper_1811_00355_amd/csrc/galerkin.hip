@@ -22,10 +22,12 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBv = 256, kBvh = 128;
 
-// packed position inside a 4^4 block
-__device__ __forceinline__ int local_of(const int l[4]) {
-  return ((l[0] + l[1] + l[2] + l[3]) & 1) * kBvh + ((l[0] + 4 * (l[1] + 4 * (l[2] + 4 * l[3]))) >> 1);
-}
+// N packed neighbours read at once (the address is a multiple of their size)
+template <typename Sp, int N>
+struct alignas(N * sizeof(Sp)) Sites {
+  Sp v[N];
+  __device__ __forceinline__ void load(const Sp* p) { *this = *reinterpret_cast<const Sites*>(p); }
+};
 
 // conj(A) W summed on matrix cores, three real products per complex one (Gauss, as
 // the restriction): with conj(A) = a + ib and W = c + id, k1 += a (c + d), k2 +=
@@ -43,26 +45,38 @@ struct Acc64 {
   __device__ __forceinline__ cx<double> get(int v) const { return {k1[v] + k2[v], k1[v] + k3[v]}; }
 };
 
-// two-spinor part of one chirality for a forward hop: upper spins as they are, lower spins as -A_mu d
-template <int MU>
-__device__ __forceinline__ void half_part(bool lower, cx<double>* f) {
-  cx<double> o[6];
-  A_mul<MU, double>(f, f + 3, o, o + 3);
+// two-spinor part of one chirality for a forward hop: upper spins as they are, lower
+// spins as -A_mu d.  A_mu only permutes and changes signs: in FP32 for narrow types.
+enum Chir { kUpper, kLower, kEither };
+template <int MU, Chir C, typename Sp, int NS>
+__device__ __forceinline__ void half_part(const Sites<Sp, NS>* s, int q, bool lower, cx<double>* f) {
+  using R = std::conditional_t<std::is_same<Sp, double2>::value, double, float>;
+  cx<R> d[6], o[6];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) f[k] = lower ? -o[k] : f[k];
+  for (int k = 0; k < 6; ++k) d[k] = ld<R, Sp>(&s[k].v[q]);
+  A_mul<MU, R>(d, d + 3, o, o + 3);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const cx<R> r = C == kUpper ? d[k] : C == kLower ? -o[k] : lower ? -o[k] : d[k];
+    f[k] = {(double)r.re, (double)r.im};
+  }
 }
 
 // One workgroup per (aggregate, 16 columns of its blocks), one wave per direction.
-// Lane (li, lk) of a wave holds, for the site lk of a group of four, the six
-// entries of row 16 rt + li (A operand) and of column li (B operand): it loads the
-// latter at x + mu, multiplies them by the link itself, and every entry is one k
-// step.  A wave first sums its face block (64 sites) and writes it, then the hops
-// inside the aggregate (192 sites) and a quarter of the clover term; the four
-// waves' parts of G are added in wave order.  Bound by the FP64 matrix products
-// (54 of them per four sites, direction and 16 columns at 2n = 40, half of their
-// peak rate); the loads are gathers of four sites from 16 vectors.  At 16^3x32, 2n =
-// 40, BF16 vectors: 1.88 ms, against 7.9 ms of nine passes over all sites that
-// wrote D lambda and restricted it.
+// Lane (li, lk) of a wave holds, for its site of a group of four, the six entries
+// of row 16 rt + li (A operand) and of column li (B operand): it loads the latter at
+// x + mu, multiplies them by the link itself, and every entry is one k step.  A
+// wave first sums its face block (64 sites) and writes it, then the hops inside
+// the aggregate (192 sites) and a quarter of the clover term; the four waves'
+// parts of G are added in wave order.  The operand loads are gathers over 16
+// vectors, one cache access a lane whatever its width, and keep the L1 busier than
+// the FP64 products do the matrix cores (54 of them per four sites, direction and 16
+// columns at 2n = 40; 47 % busy): half types take two packed neighbours to a load,
+// the others let the four lanes lk of a vector take neighbours of one line.
+// 16^3x32, 2n = 40, BF16 vectors: 1.44 ms, 1.88 with single sites in lexicographic
+// order (nine passes over all sites that wrote D lambda and restricted it: 7.9);
+// loads a whole step ahead of the products gave 1.41, but spilled in FP64.  New
+// mass on 16^4 before / after: FP64 2270 / 1966 us, FP32 1942 / 1680, BF16 1690 / 1516.
 template <int N, typename Sp>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_galerkin(
     GeomDev g, const double2* __restrict__ links, const double2* __restrict__ clov, const Sp* __restrict__ P,
@@ -87,68 +101,104 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   }
   Acc64 acc[MT];
 
-  // groups [g0, g1) of four sites of direction MU, sites ordered with MU slowest; the neighbours of a
-  // group lie in the block at nbase
-  auto hops = [&](auto mu_c, int g0, int g1, long long nbase) {
-    constexpr int MU = decltype(mu_c)::value;
-#pragma unroll 1
-    for (int gi = g0; gi < g1; ++gi) {
-      const int idx = 4 * gi + lk;
-      int l[4], e = idx;
+  // Hops in direction MU from the sites x, x + 1, .. of every lane (NS of them, packed neighbours) to y, y + 1, ..
+  auto hops = [&](auto mu_c, auto ns_c, long long x, long long y) {
+    constexpr int MU = decltype(mu_c)::value, NS = decltype(ns_c)::value;
+    Sites<Sp, NS> fr[6], ar[MT][6];
+    cx<double> u[9];
+    load_link<double, double2>(links, V, MU, x, u);
+    // (addresses opaque: the compiler would keep all of a lane's 6 (MT + 1) row addresses in registers)
+    const Sp* p = Pc + y;
+    asm volatile("" : "+v"(p));
 #pragma unroll
-      for (int d = 0; d < 4; ++d)
-        if (d != MU) {
-          l[d] = e & 3;
-          e >>= 2;
-        }
-      l[MU] = e;
-      const long long x = base + local_of(l);
-      l[MU] = (e + 1) & 3;
-      const long long y = nbase + local_of(l);
-      Sp fr[6], ar[MT][6];
-      cx<double> u[9];
+    for (int k = 0; k < 6; ++k) fr[k].load(p + k * V);
+    constexpr int AT = sizeof(Sp) == 16 && MT > 2 ? 2 : MT;   // row tiles read with the rest (registers)
+    auto rows = [&](int rt) {
+      p = Pr[rt] + x;
+      asm volatile("" : "+v"(p));
 #pragma unroll
-      for (int k = 0; k < 6; ++k) fr[k] = Pc[k * V + y];
-      load_link<double, double2>(links, V, MU, x, u);
+      for (int k = 0; k < 6; ++k) ar[rt][k].load(p + k * V);
+    };
 #pragma unroll
-      for (int rt = 0; rt < MT; ++rt)
+    for (int rt = 0; rt < AT; ++rt) rows(rt);
+    __builtin_amdgcn_sched_barrier(0);   // every load is issued before the first product
 #pragma unroll
-        for (int k = 0; k < 6; ++k) ar[rt][k] = Pr[rt][k * V + x];
-      __builtin_amdgcn_sched_barrier(0);   // every load is issued before the first product
+    for (int q = 0; q < NS; ++q) {
       cx<double> f[6], wv[6];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) f[k] = ld<double, Sp>(&fr[k]);
-      half_part<MU>(clow, f);
+      if (q) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_link<double, double2>(links, V, MU, x + q, u);
+      }
+      half_part<MU, kEither>(fr, q, clow, f);
       su3_mul_half<double>(u, f, wv);
+      if (AT < MT && q == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        rows(MT - 1);
+      }
 #pragma unroll
       for (int rt = 0; rt < MT; ++rt) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) f[k] = ld<double, Sp>(&ar[rt][k]);
-        half_part<MU>(rlow[rt], f);
+        if (16 * rt + 15 < N) half_part<MU, kUpper>(ar[rt], q, false, f);
+        else if (16 * rt >= N) half_part<MU, kLower>(ar[rt], q, true, f);
+        else half_part<MU, kEither>(ar[rt], q, rlow[rt], f);
 #pragma unroll
         for (int k = 0; k < 6; ++k) acc[rt].add(f[k], wv[k]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
+  // the pair of packed sites with the same (y, z, t) and parity: x = x0, x0 + 2, x0 = (parity + y + z + t) % 2
+  auto pair_at = [&](int par, int cy, int cz, int ct4) { return par * kBvh + 2 * (cy + 4 * (cz + 4 * ct4)); };
   auto direction = [&](auto mu_c) {
     constexpr int MU = decltype(mu_c)::value;
+    constexpr int NS = sizeof(Sp) <= 4 ? 2 : 1;   // sites of a lane's load
+    const int e = g.blk_nbr[MU * g.Vc + X];
+    const long long nb = (long long)(e & DD_SLOT_MASK) * kBv;
+    const double coef = (e & DD_WRAP_BIT) ? -0.5 * g.bc_t : -0.5;
 #pragma unroll
     for (int rt = 0; rt < MT; ++rt) acc[rt].zero();
-    const int e = g.blk_nbr[MU * g.Vc + X];
-    hops(mu_c, 48, 64, (long long)(e & DD_SLOT_MASK) * kBv);   // the face sites (coordinate MU = 3)
-    const double coef = (e & DD_WRAP_BIT) ? -0.5 * g.bc_t : -0.5;
-    double2* out = Dc + ((long long)X * 9 + 1 + MU) * NC * NC;
-#pragma unroll
-    for (int rt = 0; rt < MT; ++rt) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = 16 * rt + lk + 4 * v;
-        const cx<double> o = coef * acc[rt].get(v);
-        if (row < NC && col < NC) out[col * NC + row] = make_double2(o.re, o.im);
+    // first the hops across the face, summed by themselves, then those inside the aggregate
+#pragma unroll 1
+    for (int inside = 0; inside < 2; ++inside) {
+      if constexpr (MU == 0) {
+        // the pairs x = 1, 3: the second site hops across the face, the first one to the other pair's second site
+#pragma unroll 1
+        for (int i = 0; i < 16; ++i) {
+          const int cz = i & 3, t = i >> 2, par = (lk + cz + t + 1) & 1;
+          const int q = pair_at(par, lk, cz, t), r = pair_at(par ^ 1, lk, cz, t);
+          hops(mu_c, std::integral_constant<int, 1>(), base + q + (inside ? 0 : 1), inside ? base + r + 1 : nb + r);
+        }
+        if (inside)   // the pairs x = 0, 2 to the pairs 1, 3
+#pragma unroll 1
+          for (int i = 0; i < 32 / NS; ++i) {
+            const int h = NS == 1 ? lk & 1 : 0, cy = NS == 1 ? 2 * (i & 1) + (lk >> 1) : lk, j = NS == 1 ? i >> 1 : i;
+            const int cz = j & 3, t = j >> 2, par = (cy + cz + t) & 1;
+            hops(mu_c, std::integral_constant<int, NS>(), base + pair_at(par, cy, cz, t) + h,
+                 base + pair_at(par ^ 1, cy, cz, t) + h);
+          }
+      } else {
+        // coordinate MU slowest: 0 .. 2 stay inside
+#pragma unroll 1
+        for (int i = inside ? 0 : 48 / NS; i < (inside ? 48 / NS : 64 / NS); ++i) {
+          const int h = NS == 1 ? lk & 1 : 0, a = NS == 1 ? 2 * (i & 1) + (lk >> 1) : lk, j = NS == 1 ? i >> 1 : i;
+          const int c = j >> 3, o = j & 3, par = (j >> 2) & 1, d = (c + 1) & 3;
+          const int q = MU == 1 ? pair_at(par, c, a, o) : MU == 2 ? pair_at(par, a, c, o) : pair_at(par, a, o, c);
+          const int r = MU == 1 ? pair_at(par ^ 1, d, a, o) : MU == 2 ? pair_at(par ^ 1, a, d, o) : pair_at(par ^ 1, a, o, d);
+          hops(mu_c, std::integral_constant<int, NS>(), base + q + h, (inside ? base : nb) + r + h);
+        }
       }
-      acc[rt].zero();
+      if (inside) break;
+      double2* out = Dc + ((long long)X * 9 + 1 + MU) * NC * NC;
+#pragma unroll
+      for (int rt = 0; rt < MT; ++rt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = 16 * rt + lk + 4 * v;
+          const cx<double> o = coef * acc[rt].get(v);
+          if (row < NC && col < NC) out[col * NC + row] = make_double2(o.re, o.im);
+        }
+        acc[rt].zero();
+      }
     }
-    hops(mu_c, 0, 48, base);
   };
   switch (w) {
     case 0: direction(std::integral_constant<int, 0>()); break;
