@@ -440,6 +440,9 @@ void launch_dirac_f32_in(const GeomDev& g, const OpSet& ops64, int nrhs, const f
 void launch_sap(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                 const void* b, void* x, int wpe, int dom_rhs, int persist, hipStream_t st);
 bool sap_dom_supported(const GeomDev& g, dd_dtype dt);
+bool sap_split_use(const GeomDev& g);                          // small domains (sap_split.hip)
+void launch_sap_split(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
+                      const void* b, void* x, hipStream_t st);
 bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs);   // supported and the better form
 void launch_sap_dom(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                     const void* b, void* x, int rhs_group, bool persist, hipStream_t st);
