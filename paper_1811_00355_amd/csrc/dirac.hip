@@ -291,12 +291,16 @@ __device__ __forceinline__ void clover_rows(const S* C, const cx<float>* in, cx<
 
 template <typename S>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_dirac_hl(
-    GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, int nrhs, const float2* __restrict__ in,
-    float2* __restrict__ out) {
+    GeomDev g, const S* __restrict__ links, const S* __restrict__ clov, int nrhs, int full, int parts,
+    const float2* __restrict__ in, float2* __restrict__ out) {
   __shared__ cx<float> sp[12][256];
   __shared__ S sc[36][256];
-  int tile, unused;
-  if (!xcd_slab_tile(g, 1, 1, tile, unused)) return;   // uniform per workgroup
+  // slab order (xcd_slab_tile): the first `full` blocks of an XCD's eighth with every right-hand side, the rest in
+  // `parts` workgroups each (see hl_split)
+  const int k = blockIdx.x >> 3, t = k - full;
+  const int kk = t < 0 ? k : full + t / parts, part = t < 0 ? 0 : t % parts, np = t < 0 ? 1 : parts;
+  const int tile = g.lex_slot[(blockIdx.x & 7) * (g.Vc / 8) + kk];
+  const int r0 = part * nrhs / np, r1 = (part + 1) * nrhs / np;
   const long long V = g.V, base = (long long)tile * 256, I = base + threadIdx.x;
   const SiteLoc s = decode_site(g, I);
   unsigned J[8];   // packed neighbour indices (V < 2^32)
@@ -317,7 +321,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 #pragma unroll
   for (int e = 0; e < 36; ++e) sc[e][threadIdx.x] = clov[(long long)e * V + I];
 #pragma unroll 1
-  for (int r = 0; r < nrhs; ++r) {
+  for (int r = r0; r < r1; ++r) {
     const float2* x = in + (long long)r * 12 * V;
     cx<float> psi[12], acc[12];
     load_spinor<float, float2>(x, V, I, psi);
@@ -396,17 +400,38 @@ static void blk_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nr
   }
 }
 
+// Blocks of an XCD (32 CUs, two workgroups each) beyond whole rounds of 64 would take a
+// round of all right-hand sides, most of the chip idle: they are split over the
+// right-hand sides, into the number of workgroups with the least rounds times work
+// (a block's links and clover cost about as much as one right-hand side).  us before /
+// after, BF16: 24^3x48 (4 left of 324) five right-hand sides 388 / 361, twelve 868 / 789;
+// 24^4 (34 of 162, in three) twelve 439 / 414; 8^4 (2) two 18.2 / 12, twelve 78.5 / 12.8;
+// none left over, 16^3x32: 60 / 60.
+static void hl_split(int blocks, int nrhs, int& full, int& parts) {
+  constexpr int kSlots = 64;
+  const int rest = blocks % kSlots;
+  full = blocks - rest;
+  parts = 1;
+  int best = 1 << 30;
+  for (int p = 1; p <= std::min(nrhs, kSlots); ++p) {
+    const int cost = ((rest * p + kSlots - 1) / kSlots) * (1 + (nrhs + p - 1) / p);
+    if (cost < best) best = cost, parts = p;
+  }
+}
+
 static void dirac_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, const void* in, void* out,
                            int threads, hipStream_t st) {
   if (g.Bv == 256 && g.Vc % 16 == 0 && nrhs >= 2 && (dt == DD_F16 || dt == DD_BF16)) {
     // operator in registers across the right-hand sides
-    const unsigned nb = xcd_grid(g.Vc, 1);
+    int full, parts;
+    hl_split(g.Vc / 8, nrhs, full, parts);
+    const unsigned nb = 8 * (full + (g.Vc / 8 - full) * parts);
     if (dt == DD_F16)
-      k_dirac_hl<__half2><<<nb, 256, 0, st>>>(g, (const __half2*)ops.links, (const __half2*)ops.clover, nrhs,
-                                               (const float2*)in, (float2*)out);
+      k_dirac_hl<__half2><<<nb, 256, 0, st>>>(g, (const __half2*)ops.links, (const __half2*)ops.clover, nrhs, full,
+                                               parts, (const float2*)in, (float2*)out);
     else
-      k_dirac_hl<bf16x2><<<nb, 256, 0, st>>>(g, (const bf16x2*)ops.links, (const bf16x2*)ops.clover, nrhs,
-                                              (const float2*)in, (float2*)out);
+      k_dirac_hl<bf16x2><<<nb, 256, 0, st>>>(g, (const bf16x2*)ops.links, (const bf16x2*)ops.clover, nrhs, full,
+                                              parts, (const float2*)in, (float2*)out);
     return;
   }
   if (g.Bv == 256 && g.Vc % 16 == 0) {   // block form, slab order over the blocks
