@@ -59,9 +59,9 @@ def test_against_the_oracle(ctx, L, blk, nrhs, bc):
 
 
 @pytest.mark.parametrize("dtype", [0, 1, 2, 3])
-@pytest.mark.parametrize("L,blk", [((4, 4, 4, 4), (2, 2, 2, 2)), ((16, 16, 16, 8), (2, 2, 2, 2)),
+@pytest.mark.parametrize("L,blk", [((4, 4, 4, 4), (2, 2, 2, 2)), ((8, 8, 8, 8), (2, 2, 2, 2)), ((16, 16, 16, 8), (2, 2, 2, 2)),
                                    ((16, 8, 16, 16), (2, 2, 2, 4)), ((16, 8, 16, 16), (4, 2, 4, 2)),
-                                   ((8, 8, 16, 16), (4, 4, 4, 2))])
+                                   ((8, 8, 8, 16), (4, 4, 4, 2))])
 def test_alone_and_in_a_batch_same_bits(ctx, dtype, L, blk):
     import torch
     from paper_1811_00355_amd import Gauge
