@@ -130,7 +130,9 @@ void dd_mg_params_default(dd_mg_params* p);
  * only the FGMRES outer iteration count can see (the outer solver is flexible,
  * Sec. 2). */
 typedef struct {
-  int32_t sap_wpe;        /* SAP waves per SIMD the registers allow: 2 or 3          */
+  int32_t sap_wpe;        /* SAP waves per SIMD the registers allow: 2 or 3 (no effect on domains of at
+                             most 64 sites, or 128 on at most 64 domains per colour, which have one
+                             form of their own) */
   int32_t dirac_threads;  /* D apply workgroup size, 64, 128 or 256 (blocks other than 4^4; 4^4 blocks
                              take one 256-thread workgroup per block)                */
   int32_t coarse_spw;     /* coarse apply on half matrix cores (coarse_mfma_half): target waves per

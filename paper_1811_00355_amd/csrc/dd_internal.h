@@ -421,7 +421,8 @@ void launch_pack_fine(const GeomDev& g, dd_dtype vt, int nrhs, const double2* ca
 void launch_unpack_fine(const GeomDev& g, dd_dtype vt, int nrhs, const void* packed, double2* canon,
                         hipStream_t st);
 void launch_pack_links(const GeomDev& g, const double2* canon, double2* links64, hipStream_t st);
-// FP64 source for DD_F64 / DD_F32 targets, FP32 source for DD_F16 / DD_BF16 targets
+// FP64 source for DD_F64 / DD_F32 targets; for DD_F16 / DD_BF16 targets the FP32 source,
+// or without one the FP64 source through an FP32 rounding
 void launch_convert_pairs(dd_dtype to, const double2* src64, const float2* src32, void* dst, long long count,
                           hipStream_t st);
 void launch_vec_convert(dd_dtype from, dd_dtype to, const void* src, void* dst, long long count,
