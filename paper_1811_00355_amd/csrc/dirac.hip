@@ -202,10 +202,11 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
   }
 }
 
-// Block form (4^4 blocks: one workgroup of Bv = 256 threads per block and
+// Block form (blocks of 256 sites: one workgroup of Bv = 256 threads per block and
 // right-hand side).  The block's spinors and its first NF faces' half spinors
-// are staged in LDS once; hops read them there, so memory sees one read of every
-// spinor plus the faces.  NF (see blk_launch) is what leaves the CU its workgroups:
+// (4^4 blocks only, see face_load) are staged in LDS once; hops read them there, so
+// memory sees one read of every spinor plus the faces.  NF (see blk_launch) is what
+// leaves the CU its workgroups:
 // all eight faces in FP32 (48 KB), x and y in FP64 (72 KB; the z and t faces are whole
 // lines, and their blocks run far apart in the slab order).  Bound by traffic:
 // at 32^3x64, FP64, twelve right-hand sides, about 31 GB a launch (2.6 times the
@@ -373,7 +374,8 @@ constexpr double kDiracFlopsPerSite = 1320.0 + 504.0 + 24.0;
 // Faces in LDS: x and y in FP64, all in FP32, none for half operands (their launch
 // moves half the bytes, and the halos gave nothing) and none on lattices of at
 // most 256 blocks, which run together anyway, so that the faces would be one more
-// latency.  (By the lattice and not by the launch: the two forms round differently,
+// latency.  None either for blocks of 256 sites with other edges than four, whose
+// faces do not have face_load's 64 sites.  (By the lattice and not by the launch: the two forms round differently,
 // and a right-hand side has the same bits in every batch.)  us, without / with faces:
 // FP64 32^3x64 one right-hand side 733 / 697, twelve 6522 / 6125 (5862 with streamed
 // outputs and far neighbours); FP32 24^3x48 113 / 103,
@@ -384,9 +386,9 @@ void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, vo
   const S* L = (const S*)ops.links;
   const S* C = (const S*)ops.clover;
   constexpr int NF = sizeof(R) == 8 ? 4 : sizeof(S) == 8 ? 8 : 0;
-  const bool few = g.Vc <= 256;
-  auto* fn = nrhs == 1 ? (few ? k_dirac_blk<R, S, Tv, To, true, 0> : k_dirac_blk<R, S, Tv, To, true, NF>)
-                       : (few ? k_dirac_blk<R, S, Tv, To, false, 0> : k_dirac_blk<R, S, Tv, To, false, NF>);
+  const bool faces = g.Vc > 256 && g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
+  auto* fn = nrhs == 1 ? (faces ? k_dirac_blk<R, S, Tv, To, true, NF> : k_dirac_blk<R, S, Tv, To, true, 0>)
+                       : (faces ? k_dirac_blk<R, S, Tv, To, false, NF> : k_dirac_blk<R, S, Tv, To, false, 0>);
   fn<<<nb, 256, 0, st>>>(g, L, C, nrhs, (const Tv*)in, (To*)out);
 }
 
