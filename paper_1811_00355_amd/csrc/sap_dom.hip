@@ -26,6 +26,9 @@
 // kept out of registers between hops.
 #include <hip/hip_cooperative_groups.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "dslash.h"
 #include "ktimer.h"
 
@@ -527,15 +530,36 @@ int persist_grid(const GeomDev& g) {
   return n;
 }
 
+// Rounds of the chip that the form with G = 4 takes (256 workgroups at a time), in
+// rounds of full groups: all groups in one workgroup per domain, or one workgroup per
+// group (split).  Short last groups then save no time where every second workgroup
+// has one (an even number of groups: they meet full ones on the same CUs each round);
+// otherwise they fill the last round up.
+double rounds4(int ndom, int nrhs, bool split) {
+  static const double kLast[4] = {0.63, 0.75, 0.9, 1.0};   // a group of 1 .. 4 right-hand sides
+  const int groups = (nrhs + 3) / 4;
+  double last = kLast[(nrhs - 1) % 4];
+  if (!split || groups == 1) return std::ceil(ndom / 256.0) * (groups - 1 + last);
+  const double w = (double)ndom * groups / 256.0;
+  double rounds = std::ceil(w);
+  if (groups % 2 == 0) last = std::max(last, 0.92);
+  else if (last < 1.0) rounds = std::min(rounds, w + 0.5);
+  return rounds * (groups - 1 + last) / groups;
+}
+
 // Workgroups per domain: one for all right-hand sides when there are domains
 // enough for several rounds of the chip (each then stages its operator once),
-// one per group of G right-hand sides otherwise.  The chip holds 512 workgroups
-// of the two-RHS form; a group takes 65-85 us and the staging about 3 us, so
-// with few domains the serial loop over the groups leaves CUs idle or ends in a
-// part-filled round.  12 right-hand sides, BF16, us per launch with one / all
-// workgroups per domain: 8 domains (8^4) 401 / 71, 256 (16^3x32) 434 / 265, 864
-// (24^3x32) 1014 / 947, 1296 (24^3x48) 1529 / 1386, 4096 (32^3x64) 4106 / 4153.
-int dom_parts(int ndom, int groups) { return ndom <= 2048 ? groups : 1; }
+// one per group of G right-hand sides otherwise.  With few domains the serial loop
+// over the groups leaves CUs idle or ends in a part-filled round.  G = 2, 512 workgroups
+// on the chip: 12 right-hand sides, BF16, us per launch with one / all workgroups per
+// domain: 32 domains 383 / 73, 256 414 / 257, 864 953 / 869, 1296 1437 / 1267, 2048 1937 / 1937, 4096
+// 3873 / 3866.  G = 4 by the rounds: FP16, 192 domains five 149 / 176, eight 182 / 184, thirteen
+// 325 / 276; 288 five 292 / 265; 648 five 456 / 545, nine 737 / 678; 1296 five 932 / 1027, twelve
+// 1702 / 1550; FP32, 512 five 332 / 370, nine 519 / 557.
+int dom_parts(int ndom, int nrhs, int G) {
+  if (ndom > 2048 || (G == 4 && rounds4(ndom, nrhs, true) > 0.999 * rounds4(ndom, nrhs, false))) return 1;
+  return (nrhs + G - 1) / G;
+}
 
 template <typename S, int G, bool CG>
 void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, const void* b, void* x, bool persist,
@@ -560,7 +584,7 @@ void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, c
                                               dim3(kBvh * G), args, 0, st));
     return;
   }
-  const int parts = dom_parts(g.Vch, (nrhs + G - 1) / G);
+  const int parts = dom_parts(g.Vch, nrhs, G);
   const unsigned nb = xcd_grid(g.Vch, parts);
   for (int s = 0; s < sweeps; ++s)
     for (int colour = 0; colour < 2; ++colour)

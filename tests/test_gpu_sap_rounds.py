@@ -1,0 +1,32 @@
+"""Smoother on 4^4 domains, up to four right-hand sides per workgroup: the launch by rounds of
+the chip.  The groups of a batch share a workgroup or have one each; the bits are the
+per-RHS kernel's always."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [2, 3])
+@pytest.mark.parametrize("L,batches", [((16, 16, 16, 24), (5, 8, 13)), ((16, 16, 24, 24), (5, 9))])
+def test_half_groups_together_or_apart(L, batches, dtype):
+    import torch
+    from paper_1811_00355_amd import Context, Gauge, default_params
+    from workloads import su3_random
+    V = int(np.prod(L))
+    ctx = Context(0)
+    g = Gauge(ctx, L, (4, 4, 4, 4), np.resize(su3_random(4096 * 4 + 12, 0.3, 7), (V * 4, 3, 3)).reshape(V, 4, 3, 3), -0.1, 1.0)
+    p = default_params(block=(4, 4, 4, 4), sap_sweeps=1, sap_mr_iters=2)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    for n in batches:
+        b, x0 = (torch.randn((n, 12, V), generator=gen, device="cuda", dtype=torch.complex64) for _ in "bx")
+        out = []
+        for dom in (4, 0):
+            g.dd_gauge_set_tuning(**dict(g.dd_gauge_get_tuning(), sap_dom_rhs=dom))
+            out.append(x0.clone())
+            g.dd_sap_smooth(p, dtype, n, b, out[-1])
+        torch.cuda.synchronize()
+        print(f"L={L} dtype={dtype} nrhs={n}: same bits {torch.equal(*out)}", flush=True)
+        assert torch.equal(*out)
+    g.destroy()
+    ctx.close()
