@@ -150,8 +150,8 @@ typedef struct {
                                 domain's operator staged in LDS, shared by the right-hand sides; half
                                 operands 2 at a time (links and inverse in LDS, two workgroups per CU)
                                 or 4 at a time (clover in LDS too, one per CU), FP32 operands 4 at a
-                                time for either value (a single right-hand side on more than 512
-                                domains per colour runs as for 0); 0 = one workgroup per (domain, RHS)
+                                time for either value (batches that would leave much of the chip idle
+                                that way run as for 0); 0 = one workgroup per (domain, RHS)
                                 in layout sap_wpe.  Same bits. */
   int32_t sap_persist;       /* with sap_dom_rhs > 0: every sweep and colour of a smoother application in
                                 one cooperative launch whose workgroups (as many as the CUs hold) meet

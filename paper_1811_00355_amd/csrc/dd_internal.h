@@ -444,7 +444,7 @@ bool sap_dom_supported(const GeomDev& g, dd_dtype dt);
 bool sap_split_use(const GeomDev& g);                          // small domains (sap_split.hip)
 void launch_sap_split(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                       const void* b, void* x, hipStream_t st);
-bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs);   // supported and the better form
+bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs, int mr_iters);   // supported and the better form
 void launch_sap_dom(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int sweeps, int mr_iters,
                     const void* b, void* x, int rhs_group, bool persist, hipStream_t st);
 // transfer and coarse construction

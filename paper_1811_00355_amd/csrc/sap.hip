@@ -268,7 +268,7 @@ void launch_sap(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, int s
     launch_sap_split(g, dt, ops, nrhs, sweeps, mr_iters, b, x, st);
     return;
   }
-  if (dom_rhs > 0 && sap_dom_use(g, dt, nrhs)) {   // domain-resident form (sap_dom.hip)
+  if (dom_rhs > 0 && sap_dom_use(g, dt, nrhs, mr_iters)) {   // domain-resident form (sap_dom.hip)
     launch_sap_dom(g, dt, ops, nrhs, sweeps, mr_iters, b, x, dom_rhs, persist != 0, st);
     return;
   }

@@ -555,7 +555,7 @@ double rounds4(int ndom, int nrhs, bool split) {
 // domain: 32 domains 383 / 73, 256 414 / 257, 864 953 / 869, 1296 1437 / 1267, 2048 1937 / 1937, 4096
 // 3873 / 3866.  G = 4 by the rounds: FP16, 192 domains five 149 / 176, eight 182 / 184, thirteen
 // 325 / 276; 288 five 292 / 265; 648 five 456 / 545, nine 737 / 678; 1296 five 932 / 1027, twelve
-// 1702 / 1550; FP32, 512 five 332 / 370, nine 519 / 557.
+// 1702 / 1550; FP32, 512 five 323 / 372, nine 515 / 560.
 int dom_parts(int ndom, int nrhs, int G) {
   if (ndom > 2048 || (G == 4 && rounds4(ndom, nrhs, true) > 0.999 * rounds4(ndom, nrhs, false))) return 1;
   return (nrhs + G - 1) / G;
@@ -592,14 +592,30 @@ void run_dom(const GeomDev& g, const OpSet& ops, int nrhs, int sweeps, int mr, c
                (k_sap_dom<S, G, CG, false><<<nb, kBvh * G, 0, st>>>(g, L, C, I, nrhs, parts, colour, 1, mr, bb, xx)));
 }
 
+// FP32 operands have two forms with the same bits: this one, in rounds of 256
+// workgroups, and the per-RHS kernel, about 1024 workgroups at a time.  A round that is
+// nearly empty, or a last group of one or two right-hand sides, costs this form most
+// of a full round, so a batch takes the form whose estimated launch is shorter.  us
+// at four MR steps, fitted to 45 lattices of 8 to 2048 domains per colour with 1 to 17
+// right-hand sides (3.5 % rms each), the dependence on the steps to 24 to 648 domains.
+// Measured per launch, per RHS / here: 192 domains four right-hand sides 118 / 95, five
+// 129 / 151, eight 230 / 181; 288 two 126 / 142, four 215 / 182, twelve 479 / 382; 648 one 152 / 195,
+// five 499 / 483, eight 736 / 600; 1296 one 345 / 405, two 454 / 471, five 937 / 982, nine 1575 / 1340;
+// 256 (16^3x32) one 106 / 67, three 124 / 86, twelve 435 / 284.
+double dom_f32_us(int ndom, int nrhs, int mr) {
+  const double full = std::min(rounds4(ndom, nrhs, false), ndom > 2048 ? HUGE_VAL : rounds4(ndom, nrhs, true));
+  return (86.0 * full + 0.0073 * ndom * nrhs + 0.045 * ndom) * (mr + 3.55) / 7.55;
+}
+double per_rhs_f32_us(int ndom, int nrhs, int mr) {
+  const double w = (double)ndom * nrhs, full = w <= 1024 ? 0.0 : std::floor(w / 1008);   // rounds before the last
+  return (84.0 + 120.0 * full + 39.0 * (w / 1008 - full) + 0.075 * ndom) * (mr + 2.64) / 6.64;
+}
+
 }  // namespace
 
-// FP32 operands, one right-hand side on lattices of several rounds of domains: three
-// of the form's four right-hand-side slots would idle, and the per-RHS kernel
-// (the same bits) keeps more domains on a CU.  us per launch, per RHS / domain form:
-// 24^3x48 one right-hand side 340 / 407, four 787 / 625; 16^3x32 104 / 67.
-bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs) {
-  return sap_dom_supported(g, dt) && !(dt == DD_F32 && nrhs == 1 && g.Vch > 512);
+bool sap_dom_use(const GeomDev& g, dd_dtype dt, int nrhs, int mr_iters) {
+  return sap_dom_supported(g, dt) &&
+         (dt != DD_F32 || dom_f32_us(g.Vch, nrhs, mr_iters) <= 1.01 * per_rhs_f32_us(g.Vch, nrhs, mr_iters));
 }
 
 bool sap_dom_supported(const GeomDev& g, dd_dtype dt) {
