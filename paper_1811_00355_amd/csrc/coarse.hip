@@ -467,19 +467,23 @@ MfmaLaunch<float> half_launch(int spw, int count) {
 //    (at 2n = 40 12 waves per site), and the blocks are kept cached for the next apply;
 //  - they do not: HBM bounds it, so two direction groups whose waves take all
 //    row tiles of a site (its x is loaded once per direction instead of once per
-//    tile) and stream the blocks past the caches.
+//    tile) and stream the blocks past the caches, unless another 16 right-hand
+//    sides read them again (us, twenty right-hand sides, streamed / cached: 2n = 40,
+//    24^3x48 137 / 119, 32^3x64 398 / 339; 2n = 48, 24^3x48 180 / 166; twelve, 32^3x64 206 either way).
 // Measured full applies, us, first / second split, 12 right-hand sides, FP32
 // blocks: 2n = 40 on 88 MB (16x16x24x32) 20 / 25, 199 MB (24^3x32) 40 / 49,
 // 299 MB (24^3x48) 76 / 71, 708 MB (32^3x48) 179 / 156; 2n = 48 on 430 MB 111 / 94.
 constexpr double kCachedStencilBytes = 256e6;
 
 template <int NC, typename Sd, typename R>
-MfmaLaunch<R> full_launch(int Vc, int count, bool inv) {
+MfmaLaunch<R> full_launch(int Vc, int count, bool inv, int nrhs) {
   constexpr int MT = (NC + 15) / 16;
   const bool cached = 9.0 * Vc * NC * NC * sizeof(Sd) <= kCachedStencilBytes;
   MfmaFn<R> fn;
   if (cached)
     fn = inv ? (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, true, 4, 1, false> : (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, false, 4, 1, false>;
+  else if (nrhs > 16)
+    fn = inv ? (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, true, 2, MT, false> : (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, false, 2, MT, false>;
   else
     fn = inv ? (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, true, 2, MT, true> : (MfmaFn<R>)k_coarse_mfma<NC, Sd, R, false, 2, MT, true>;
   const unsigned per_x = (count + 7) / 8;
@@ -496,8 +500,8 @@ MfmaLaunch<R> full_launch(int Vc, int count, bool inv) {
     default: return CALL(48);   \
   }
 template <typename Sd, typename R>
-MfmaLaunch<R> full_pick(int nc, int Vc, int count, bool inv) {
-#define DD_FULL(N) (full_launch<N, Sd, R>(Vc, count, inv))
+MfmaLaunch<R> full_pick(int nc, int Vc, int count, bool inv, int nrhs) {
+#define DD_FULL(N) (full_launch<N, Sd, R>(Vc, count, inv, nrhs))
   DD_NC_SWITCH(nc, DD_FULL)
 #undef DD_FULL
 }
@@ -530,7 +534,7 @@ void launch_coarse_mv(const GeomDev& g, dd_dtype vt, int nc, const void* Dc, con
                        (double)count * nc * nrhs * vector_pair_bytes(vt) * (2 + (beta != 0.0 ? 1 : 0));
   const double flops = 8.0 * count * nblk * nc * nc * nrhs;
   if (vt == DD_F64) {
-    const MfmaLaunch<double> k = full_pick<double2, double>(nc, g.Vc, count, post_inv);
+    const MfmaLaunch<double> k = full_pick<double2, double>(nc, g.Vc, count, post_inv, nrhs);
     DD_TIMED("k_coarse_mv", st, bytes, flops,
              (k.fn<<<k.grid, k.blk, 0, st>>>(g, Dc, Minv, use_inv, nrhs, site_begin, count, a_self, (const double2*)xs,
                                              a_hop, (const double2*)xh, beta, (const double2*)z, (double2*)out,
@@ -538,9 +542,9 @@ void launch_coarse_mv(const GeomDev& g, dd_dtype vt, int nc, const void* Dc, con
     return;
   }
   hm = hm && (bt == DD_F16 || bt == DD_BF16);
-  const MfmaLaunch<float> k = bt == DD_F16    ? (hm ? half_pick<__half2>(nc, count, spw) : full_pick<__half2, float>(nc, g.Vc, count, post_inv))
-                              : bt == DD_BF16 ? (hm ? half_pick<bf16x2>(nc, count, spw) : full_pick<bf16x2, float>(nc, g.Vc, count, post_inv))
-                                              : full_pick<float2, float>(nc, g.Vc, count, post_inv);
+  const MfmaLaunch<float> k = bt == DD_F16    ? (hm ? half_pick<__half2>(nc, count, spw) : full_pick<__half2, float>(nc, g.Vc, count, post_inv, nrhs))
+                              : bt == DD_BF16 ? (hm ? half_pick<bf16x2>(nc, count, spw) : full_pick<bf16x2, float>(nc, g.Vc, count, post_inv, nrhs))
+                                              : full_pick<float2, float>(nc, g.Vc, count, post_inv, nrhs);
   DD_TIMED("k_coarse_mfma", st, bytes, flops,
            (k.fn<<<k.grid, k.blk, 0, st>>>(g, Dc, Minv, use_inv, nrhs, site_begin, count, (float)a_self,
                                            (const float2*)xs, (float)a_hop, (const float2*)xh, (float)beta,
