@@ -1,0 +1,76 @@
+"""Rounding of the FP64 setup arithmetic against 80-bit arithmetic on the same inputs.  A
+chain of N products of random sign is 0.4 u sqrt(N / 2) off (u = 2^-53, the partial
+sums growing as sqrt(k)), which the bars below follow from the kernels' chains."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+LD = np.clongdouble
+L, BLK = (8, 8, 8, 8), (4, 4, 4, 4)
+U53 = 2.0 ** -53
+
+
+def chain(n):
+    return 0.4 * U53 * np.sqrt(n / 2)
+
+
+def norm(z):
+    return float(np.sqrt((np.abs(z) ** 2).sum()))
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1811_00355_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def setup(ctx, n, inner=0):
+    from paper_1811_00355_amd import Gauge, MG, default_params
+    from oracle.lattice import Lattice
+    from workloads import gauss_vectors, su3_field
+    lat = Lattice(L, BLK)
+    U = su3_field(L, 0.25, 3)
+    g = Gauge(ctx, L, BLK, U, -0.25, 1.0)
+    p = default_params(block=BLK, n_vec=n, setup_iters=0, init_sap_apps=2, inner_dtype=inner, store_dtype=inner)
+    return lat, U, g, MG(g, p, tv_host=gauss_vectors(n, lat.V, 5).reshape(n, lat.V, 4, 3))
+
+
+@pytest.mark.parametrize("n,inner", [(8, 0), (20, 0), (20, 1)])
+def test_galerkin_operator(ctx, n, inner):
+    """Two columns of D_c from the stored P and clover.  Chains of 96 products, the links' products add 1.2 u: 3.3e-16 of
+    a block of hops; of the self block as much of each of its parts, which cancel (P is smooth)."""
+    import _gpu
+    from oracle import amg
+    from oracle.dirac import apply_clover, hop_one
+    lat, U, g, mg = setup(ctx, n, inner)
+    P = mg.export_vectors()
+    P = (_gpu.round_f32(P) if inner else P).astype(LD)
+    A = _gpu.stored_clover_dense(g.export_clover()[0], 0).astype(LD)
+    Pa = np.moveaxis(amg.to_aggregates(lat, P), 0, 2)                     # [Vc][2][n][K]
+    bar = float(np.hypot(chain(96), 1.2 * U53))
+    dc = mg.export_coarse()
+    U = U.astype(LD)
+    for t, j in ((0, n - 1), (1, 3)):
+        phi = np.zeros_like(P[0])
+        phi[:, 2 * t:2 * t + 2] = P[j][:, 2 * t:2 * t + 2]
+        parts, face = [apply_clover(A, phi)], []
+        for mu in range(4):
+            for sign, keep in ((+1, lat.inside_fwd[mu]), (-1, lat.inside_bwd[mu])):
+                h = hop_one(U, lat, phi, mu, sign)
+                parts.append(h * keep[:, None, None])
+                face.append(h * ~keep[:, None, None])
+
+        def restrict(f):
+            return (Pa.conj() * amg.to_aggregates(lat, f)[:, :, None]).sum(-1).reshape(lat.Vc, 2 * n)
+
+        got = dc[:, :, :, t * n + j]
+        parts = [restrict(f) for f in parts]
+        e0 = norm(got[:, 0] - sum(parts)) / np.sqrt(sum(norm(f) ** 2 for f in parts))
+        refs = [restrict(face[2 * mu + b]) for b in range(2) for mu in range(4)]
+        e = max(norm(got[:, 1 + d] - refs[d]) / norm(refs[d]) for d in range(8))
+        print(f"D_c n={n} inner={inner} column {t, j}: self {e0:.2e}, hops {e:.2e}, bar {bar:.2e}", flush=True)
+        assert max(e0, e) < bar
+    mg.destroy()
+    g.destroy()
