@@ -462,9 +462,15 @@ __global__ void __launch_bounds__(512) k_gram_schmidt(GeomDev g, int n, const Ti
           nrm = 1.0;
         }
         const double inv = nrm == 0.0 ? 1.0 : 1.0 / nrm;
+        // the second time the vector is normalised but for a few roundings, which inv (no finer than its last place
+        // next to one) would not take out
+        const double off = 0.5 * (1.0 - d[0].re);
+        const bool unit = pass == 1 && off * off < 1e-18;
         cx<double> f[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) f[c] = inv * v[0][c];
+        for (int c = 0; c < 3; ++c)
+          f[c] = unit ? cx<double>{__builtin_fma(off, v[0][c].re, v[0][c].re), __builtin_fma(off, v[0][c].im, v[0][c].im)}
+                      : inv * v[0][c];
         const double nf = n0[0];
 #pragma unroll
         for (int b = 1; b < B; ++b) {

@@ -74,3 +74,18 @@ def test_galerkin_operator(ctx, n, inner):
         assert max(e0, e) < bar
     mg.destroy()
     g.destroy()
+
+
+@pytest.mark.parametrize("n", [8, 20])
+def test_orthonormality(ctx, n):
+    """P^dag P - 1 of every aggregate and chirality, rms per vector: the last normalisation's norm is one within its
+    rounding (at most u) and the sums' (a third of u and less), the vectors' own rounding averages out: 1.6 u."""
+    from oracle import amg
+    lat, _, g, mg = setup(ctx, n)
+    Q = np.moveaxis(amg.to_aggregates(lat, mg.export_vectors().astype(LD)), 0, 2)
+    dev = (Q.conj()[:, :, :, None] * Q[:, :, None]).sum(-1) - np.eye(n)
+    e = norm(dev) / np.sqrt(2.0 * lat.Vc * n)
+    print(f"P^dag P - 1, n={n}: {e:.2e} a vector, bar {1.6 * U53:.2e}", flush=True)
+    assert e < 1.6 * U53
+    mg.destroy()
+    g.destroy()
