@@ -130,6 +130,10 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
   typedef typename Acc::vec Tv;
   constexpr int MT = (NC + 15) / 16, KS = NC / 4, WG = MT / TW;   // WG: waves per group
   constexpr bool kTiled = sizeof(R) == 4;   // FP64 blocks are column major
+  // FP64: two chains for a block's columns, added before they meet the other directions, and the self term last.  Against
+  // 80 bits, 2n = 16 / 40: 1.60 / 2.27e-16, a plain sum by columns 1.53 / 2.18, one chain with the self term first 2.12 /
+  // 3.06 (thirds: 1.58 / 1.99, but 3-10 % of the time; halves 0-3 %)
+  constexpr bool kFine = sizeof(R) == 8;
   constexpr int P = kTiled ? tile_group(NC, (int)sizeof(Sd)) : 1;
   struct alignas(P * sizeof(Sd)) Pack {
     Sd v[P];
@@ -147,6 +151,7 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
   const int X = site_begin + local;
   const long long vstride = (long long)g.Vc * NC;
   const int d_begin = a_self != (R)0 ? 0 : 1, d_end = a_hop != (R)0 ? 9 : 1;
+  const int nd = d_end - d_begin;
   const int li = lane & 15, lk = lane >> 4;
   // rows 16 t + li, columns lk KS + ks of a block
   auto load_rows = [&](const Sd* B, int t, Rows& r) {
@@ -182,7 +187,8 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
 #pragma unroll
       for (int v = 0; v < 4; ++v) tot[i][v] = {(R)0, (R)0};
 #pragma unroll 1
-    for (int d = d_begin + q; d < d_end; d += DS) {
+    for (int p = q; p < nd; p += DS) {
+      const int d = !kFine ? d_begin + p : p + 1 == nd && d_begin == 0 ? 0 : p + 1;
       const int Y = d == 0 ? X : __builtin_amdgcn_readfirstlane(g.blk_nbr[(d - 1) * g.Vc + X] & DD_SLOT_MASK);
       const Tv* xp = (d == 0 ? xs : xh) + roff + (long long)Y * NC;
       const Sd* B = d == 0 && use_inv ? Mx : Dc + ((long long)X * 9 + d) * NC * NC;
@@ -197,10 +203,18 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
 #pragma unroll
       for (int i = 0; i < TW; ++i) {
         Acc acc;
+        cx<R> part[4];
 #pragma unroll
-        for (int k = 0; k < KS; ++k) acc.add(ld<R, Sd>(&rows[i].a[k / P].v[k % P]), x[k]);
+        for (int k = 0; k < KS; ++k) {
+          acc.add(ld<R, Sd>(&rows[i].a[k / P].v[k % P]), x[k]);
+          if (kFine && k == KS / 2 - 1) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) tot[i][v] = tot[i][v] + sc * acc.get(v);
+            for (int v = 0; v < 4; ++v) part[v] = acc.get(v);
+            acc = Acc();
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tot[i][v] = tot[i][v] + sc * (kFine ? part[v] + acc.get(v) : acc.get(v));
       }
     }
     if constexpr (DS > 1) {
@@ -219,12 +233,22 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
         for (int v = 0; v < 4; ++v) {
           const int row = 16 * (t0 + i) + Acc::row(lk, v);
           cx<R> o = tot[i][v];
-          if constexpr (DS > 1)
+          if constexpr (kFine && DS > 1) {   // the group of the self term last
+            const Tv first = red[0][row][li];
+            cx<R> h = {first.x, first.y};
+#pragma unroll
+            for (int p = 1; p < DS - 1; ++p) {
+              const Tv b = red[p][row][li];
+              h = h + cx<R>{b.x, b.y};
+            }
+            o = o + h;
+          } else if constexpr (DS > 1) {
 #pragma unroll
             for (int p = 0; p < DS - 1; ++p) {
               const Tv b = red[p][row][li];
               o = o + cx<R>{b.x, b.y};
             }
+          }
           if (row < NC) {
             const long long oi = (long long)(r0 + li) * vstride + (long long)X * NC + row;
             if (li < nr && beta != (R)0) {

@@ -89,3 +89,31 @@ def test_orthonormality(ctx, n):
     assert e < 1.6 * U53
     mg.destroy()
     g.destroy()
+
+
+@pytest.mark.parametrize("n", [8, 20])
+def test_coarse_apply(ctx, n):
+    """The FP64 coarse apply on its own D_c: two chains of 2n products a block, nine blocks added up (0.4 u sqrt(5)), and
+    15 % for the spread."""
+    import torch
+    lat, _, g, mg = setup(ctx, n)
+    nc = 2 * n
+    D = mg.export_coarse().astype(LD)
+    x = np.random.default_rng(3).standard_normal((4, lat.Vc, nc, 2)).view(np.complex128)[..., 0]
+    cin = torch.from_numpy(np.ascontiguousarray(x).reshape(4, -1)).cuda()
+    pin = torch.empty((4, lat.Vc, nc), dtype=torch.complex128, device="cuda")
+    pout, out = torch.empty_like(pin), torch.empty_like(cin)
+    mg.pack_coarse(0, 4, cin, pin)
+    mg.dd_coarse_apply(0, 4, pin, pout)
+    mg.unpack_coarse(0, 4, pout, out)
+    torch.cuda.synchronize()
+    ref = np.einsum("xij,rxj->rxi", D[:, 0], x.astype(LD))
+    for mu in range(4):
+        for d, sign in ((1 + mu, +1), (5 + mu, -1)):
+            ref = ref + np.einsum("xij,rxj->rxi", D[:, d], x.astype(LD)[:, lat.coarse_neighbor(mu, sign)])
+    e = norm(out.cpu().numpy().reshape(ref.shape) - ref) / norm(ref)
+    bar = 1.15 * float(np.hypot(chain(nc), chain(10)))
+    print(f"coarse apply n={n}: {e:.2e}, bar {bar:.2e}", flush=True)
+    assert e < bar
+    mg.destroy()
+    g.destroy()
