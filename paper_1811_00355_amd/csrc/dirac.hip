@@ -35,10 +35,11 @@ __global__ void __launch_bounds__(256) k_dirac(GeomDev g, const S* __restrict__ 
 // keeps what is read again: the links (a site's forward link is its backward
 // neighbour's backward link), the spinors of x and y neighbours and, for the other
 // right-hand sides' workgroups, the operator.  The streams are the output, with one
-// right-hand side the clover operand, and with several z and t neighbours' spinors
-// where x and y ones are read ahead (FP64).  32^3x64, FP64, twelve right-hand sides: 6112
-// us without, 5950 with the output, 5862 with the neighbours as well; y neighbours
-// too 5820, but 4 % slower on 24^3x48; the own spinors too 7236.
+// right-hand side the clover operand, and with more than four z and t neighbours'
+// spinors where x and y ones are read ahead (FP64).  32^3x64, FP64, twelve right-hand
+// sides: 6112 us without, 5950 with the output, 5862 with the neighbours as well; y
+// neighbours too 5820, but 4 % slower on 24^3x48; the own spinors too 7236.  (Two and
+// three right-hand sides, 16^3x24, neighbours streamed / not: 50.5 / 47.2, 73.8 / 68.8.)
 template <typename R, typename S>
 __device__ __forceinline__ cx<R> ld_stream(const S* p) {
   return ld<R, S>(p);
@@ -212,7 +213,7 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
 // at 32^3x64, FP64, twelve right-hand sides, about 31 GB a launch (2.6 times the
 // algorithmic bytes) at 5.3 TB/s; two right-hand sides of a block in one workgroup
 // measured slower (7.2 against 6.1 ms).
-template <typename R, typename S, typename Tv, typename To, bool NT, int NF>
+template <typename R, typename S, typename Tv, typename To, bool NT, int NF, bool FAR>
 __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restrict__ links,
                                                    const S* __restrict__ clov, int nrhs, const Tv* __restrict__ in,
                                                    To* __restrict__ out) {
@@ -244,7 +245,7 @@ __global__ void __launch_bounds__(256) k_dirac_blk(GeomDev g, const S* __restric
 #pragma unroll
       for (int c = 6; c < 12; ++c) p[c] = {(R)0, (R)0};
     } else {
-      if constexpr (!NT && NF == 4) load_spinor_stream<R, Tv>(x, g.V, J, p);   // z and t neighbours
+      if constexpr (FAR) load_spinor_stream<R, Tv>(x, g.V, J, p);   // z and t neighbours
       else load_spinor<R, Tv>(x, g.V, J, p);
     }
   };
@@ -371,24 +372,30 @@ constexpr double kDiracFlopsPerSite = 1320.0 + 504.0 + 24.0;
 }  // namespace
 
 // Block form.  With one right-hand side the clover is streamed.
-// Faces in LDS: x and y in FP64, all in FP32, none for half operands (their launch
-// moves half the bytes, and the halos gave nothing) and none on lattices of at
-// most 256 blocks, which run together anyway, so that the faces would be one more
-// latency.  None either for blocks of 256 sites with other edges than four, whose
-// faces do not have face_load's 64 sites.  (By the lattice and not by the launch: the two forms round differently,
-// and a right-hand side has the same bits in every batch.)  us, without / with faces:
-// FP64 32^3x64 one right-hand side 733 / 697, twelve 6522 / 6125 (5862 with streamed
-// outputs and far neighbours); FP32 24^3x48 113 / 103,
-// twelve 1148 / 1055; 8^4 FP32 13.1 / 14.1, FP64 14.1 / 15.8.
+// Faces in LDS (the same bits as without): x and y in FP64, all in FP32, none for half
+// operands (their launch moves half the bytes, and the halos gave nothing), none on
+// lattices of at most 256 blocks, which run together anyway, so that the faces
+// would be one more latency, and none in FP64 for more than four right-hand sides on
+// up to 1024 blocks, whose vectors the last-level cache holds.  None either for blocks
+// of 256 sites with other edges than four, whose faces do not have face_load's 64
+// sites.  us, without / with faces: FP64 384 blocks (16^3x24) one right-hand side 33.7 / 31.9,
+// two 46.9 / 47.2, five 105 / 110, twelve 245 / 268; 768 (16^2x24x32) four 177 / 173, twelve 486 /
+// 517; 2592 (24^3x48) two 367 / 354, twelve 1797 / 1723; 32^3x64 one 733 / 697, twelve 6522 / 5862;
+// FP32 16^3x24 one 22.5 / 21.2, twelve 134 / 130, 24^3x48 117 / 107, 1128 / 1012; 8^4 FP32 13.1 / 14.1,
+// FP64 14.1 / 15.8.
 template <typename R, typename S, typename Tv, typename To>
 void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, void* out, hipStream_t st) {
   const unsigned nb = xcd_grid(g.Vc, nrhs);
   const S* L = (const S*)ops.links;
   const S* C = (const S*)ops.clover;
-  constexpr int NF = sizeof(R) == 8 ? 4 : sizeof(S) == 8 ? 8 : 0;
-  const bool faces = g.Vc > 256 && g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4;
-  auto* fn = nrhs == 1 ? (faces ? k_dirac_blk<R, S, Tv, To, true, NF> : k_dirac_blk<R, S, Tv, To, true, 0>)
-                       : (faces ? k_dirac_blk<R, S, Tv, To, false, NF> : k_dirac_blk<R, S, Tv, To, false, 0>);
+  constexpr bool F64 = sizeof(R) == 8;
+  constexpr int NF = F64 ? 4 : sizeof(S) == 8 ? 8 : 0;
+  const bool faces = g.Vc > 256 && g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4 &&
+                     (!F64 || nrhs <= 4 || g.Vc > 1024);
+  auto* fn = nrhs == 1 ? (faces ? k_dirac_blk<R, S, Tv, To, true, NF, false> : k_dirac_blk<R, S, Tv, To, true, 0, false>)
+             : !faces  ? k_dirac_blk<R, S, Tv, To, false, 0, false>
+             : F64 && nrhs > 4 ? k_dirac_blk<R, S, Tv, To, false, NF, F64>
+                               : k_dirac_blk<R, S, Tv, To, false, NF, false>;
   fn<<<nb, 256, 0, st>>>(g, L, C, nrhs, (const Tv*)in, (To*)out);
 }
 

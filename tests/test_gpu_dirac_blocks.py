@@ -44,6 +44,31 @@ def test_dirac_on_other_blocks_of_256_sites(blk, L, dtype):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("L", [(16, 16, 16, 64), (16, 16, 16, 72)])
+def test_batches_around_the_face_rules_same_bits(L, dtype):
+    """4^4 blocks, 1024 and 1152 of them: in FP64 one to four right-hand sides read the faces ahead, five do so on the larger
+    lattice only; every form the same bits."""
+    import torch
+    from paper_1811_00355_amd import Context, Gauge
+    from workloads import su3_random
+    V = int(np.prod(L))
+    ctx = Context(0)
+    g = Gauge(ctx, L, (4, 4, 4, 4), np.resize(su3_random(4096 * 4 + 12, 0.3, 7), (V * 4, 3, 3)).reshape(V, 4, 3, 3), -0.1, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((5, 12, V), generator=gen, device="cuda", dtype=torch.complex128 if dtype == 0 else torch.complex64)
+    out = []
+    for n in (5, 4, 2, 1):
+        print(f"D apply L={L} dtype={dtype} nrhs={n}", flush=True)
+        y = torch.empty_like(x[:n])
+        g.dd_dirac_apply(dtype, n, x[:n].contiguous(), y)
+        torch.cuda.synchronize()
+        out.append(y)
+        assert torch.equal(y, out[0][:n])
+    g.destroy()
+    ctx.close()
+
+
 def test_solve_on_other_blocks_of_256_sites():
     import torch
     import _gpu
