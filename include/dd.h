@@ -133,8 +133,8 @@ typedef struct {
   int32_t sap_wpe;        /* SAP waves per SIMD the registers allow: 2 or 3 (no effect on domains of at
                              most 64 sites, or 128 on at most 64 domains per colour, which have one
                              form of their own) */
-  int32_t dirac_threads;  /* D apply workgroup size, 64, 128 or 256 (blocks other than 4^4; 4^4 blocks
-                             take one 256-thread workgroup per block)                */
+  int32_t dirac_threads;  /* D apply workgroup size, 64, 128 or 256 (blocks of fewer than 256 sites; those
+                             of 256 take one 256-thread workgroup per block)         */
   int32_t coarse_spw;     /* coarse apply on half matrix cores (coarse_mfma_half): target waves per
                              workgroup, 2, 4 or 8 (sites per workgroup =
                              max(1, coarse_spw / ceil(2n / 16)), at most 4); other forms ignore it */
@@ -292,9 +292,10 @@ dd_status dd_solve_bicgstab(dd_gauge* g, const dd_bicgstab_params* p, int nrhs, 
 
 /* ---- autotuner --------------------------------------------------------------------------
  * dd_autotune times every launch-shape candidate of the smoother (waves per
- * SIMD, domain-resident form), the FP64 D apply (workgroup size) and the coarse stencil on matrix
- * cores (sites per workgroup, in the coarse block type the tuning already
- * selects) on this setup's own operators and workspace for nrhs right-hand
+ * SIMD, domain-resident form), the FP64 D apply (workgroup size) and the coarse
+ * stencil on half matrix cores (waves per workgroup), where this setup's launches
+ * read the choice (the others keep their values),
+ * on this setup's own operators and workspace for nrhs right-hand
  * sides, keeps the fastest in the gauge field (shared by every setup on it)
  * and returns a text report (report may be NULL).  The numerical choices
  * coarse_half, coarse_basis_half and coarse_mfma_half are the caller's and are

@@ -1292,41 +1292,42 @@ dd_status dd_autotune(dd_mg* mg, int nrhs, const char* cache_path, char* report,
     char line[160];
     const dd_dtype od = op_dtype(mg), vt = inner_vt(mg);
     Tuning best = g->tune;
+    // Only choices that a launch reads are timed; the others stay as they were.
     // SAP: one sweep over scratch vectors of the workspace; the per-RHS layouts,
-    // then (4^4 domains, half-precision operands) the domain-resident form
-    if (od != DD_F64) {
+    // then (4^4 domains) the domain-resident form
+    if (od != DD_F64 && !sap_split_use(G)) {
+      const int mr = mg->p.sap_mr_iters;
       float bt = 1e30f;
-      best.sap_dom_rhs = 0;
+      int dom = 0;
       for (int wpe : {2, 3}) {
-        float t =
-            time_ms([&] { launch_sap(G, od, g->ops[od], nrhs, 1, mg->p.sap_mr_iters, w->vin, w->xs, wpe, 0, 0, st); });
+        float t = time_ms([&] { launch_sap(G, od, g->ops[od], nrhs, 1, mr, w->vin, w->xs, wpe, 0, 0, st); });
         std::snprintf(line, sizeof(line), "k_sap_colour sap_wpe=%d %.3f ms/sweep\n", wpe, t);
         rep += line;
         if (t < bt) bt = t, best.sap_wpe = wpe;
       }
-      if (sap_dom_supported(G, od)) {
-        for (int dr : {4, 2}) {
-          float t =
-              time_ms([&] { launch_sap(G, od, g->ops[od], nrhs, 1, mg->p.sap_mr_iters, w->vin, w->xs, 2, dr, 0, st); });
+      if (sap_dom_use(G, od, nrhs, mr)) {
+        const std::vector<int> forms = od == DD_F32 ? std::vector<int>{4} : std::vector<int>{4, 2};   // FP32: one form
+        for (int dr : forms) {
+          float t = time_ms([&] { launch_sap(G, od, g->ops[od], nrhs, 1, mr, w->vin, w->xs, 2, dr, 0, st); });
           std::snprintf(line, sizeof(line), "k_sap_dom sap_dom_rhs=%d %.3f ms/sweep\n", dr, t);
           rep += line;
-          if (t < bt) bt = t, best.sap_dom_rhs = dr;
+          if (t < bt) bt = t, dom = dr;
         }
+        best.sap_dom_rhs = dom;
         // the chosen domain form as one cooperative launch of all the smoother's sweeps
         best.sap_persist = 0;
-        if (best.sap_dom_rhs) {
+        if (dom) {
           const int sw = mg->p.sap_sweeps > 0 ? mg->p.sap_sweeps : 1;
-          float t = time_ms([&] {
-            launch_sap(G, od, g->ops[od], nrhs, sw, mg->p.sap_mr_iters, w->vin, w->xs, 2, best.sap_dom_rhs, 1, st);
-          }) / sw;
-          std::snprintf(line, sizeof(line), "k_sap_dom_persist sap_dom_rhs=%d %.3f ms/sweep\n", best.sap_dom_rhs, t);
+          float t =
+              time_ms([&] { launch_sap(G, od, g->ops[od], nrhs, sw, mr, w->vin, w->xs, 2, dom, 1, st); }) / sw;
+          std::snprintf(line, sizeof(line), "k_sap_dom_persist sap_dom_rhs=%d %.3f ms/sweep\n", dom, t);
           rep += line;
           if (t < bt) bt = t, best.sap_persist = 1;
         }
       }
     }
     // FP64 D apply of the outer solver
-    {
+    if (dirac_threads_read(G)) {
       float bt = 1e30f;
       for (int th : {64, 128, 256}) {
         float t = time_ms([&] { launch_dirac(G, DD_F64, g->ops[DD_F64], nrhs, w->x64, w->zt64, st, th); });
@@ -1335,17 +1336,16 @@ dd_status dd_autotune(dd_mg* mg, int nrhs, const char* cache_path, char* report,
         if (t < bt) bt = t, best.dirac_threads = th;
       }
     }
-    // coarse stencil on matrix cores, in the block type the caller chose
-    if (vt == DD_F32) {
+    // coarse stencil on half matrix cores
+    const CoarseOps c = coarse_ops(mg, vt);
+    if (vt == DD_F32 && c.hm && (c.bt == DD_F16 || c.bt == DD_BF16)) {
       float bt = 1e30f;
       for (int spw : {2, 4, 8}) {
         float t = time_ms([&] {
-          CoarseOps c = coarse_ops(mg, vt);
           launch_coarse_mv(G, vt, mg->nc, c.Dc, c.Dinv, 0, nrhs, 0, G.Vc, 1.0, w->cb, 1.0, w->cb, 0.0, nullptr, w->cw,
                            st, spw, c.bt, c.hm);
         });
-        std::snprintf(line, sizeof(line), "k_coarse_mfma coarse_spw=%d%s %.3f ms\n", spw,
-                      g->tune.coarse_half && mg->Dch ? " (half blocks)" : "", t);
+        std::snprintf(line, sizeof(line), "k_coarse_mfma coarse_spw=%d (half blocks) %.3f ms\n", spw, t);
         rep += line;
         if (t < bt) bt = t, best.coarse_spw = spw;
       }

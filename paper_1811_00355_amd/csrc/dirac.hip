@@ -428,9 +428,12 @@ static void hl_split(int blocks, int nrhs, int& full, int& parts) {
   }
 }
 
+// blocks of 256 sites have a workgroup each, in slab order
+bool dirac_threads_read(const GeomDev& g) { return g.Bv != 256 || g.Vc % 16 != 0; }
+
 static void dirac_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int nrhs, const void* in, void* out,
                            int threads, hipStream_t st) {
-  if (g.Bv == 256 && g.Vc % 16 == 0 && nrhs >= 2 && (dt == DD_F16 || dt == DD_BF16)) {
+  if (!dirac_threads_read(g) && nrhs >= 2 && (dt == DD_F16 || dt == DD_BF16)) {
     // operator in registers across the right-hand sides
     int full, parts;
     hl_split(g.Vc / 8, nrhs, full, parts);
@@ -443,7 +446,7 @@ static void dirac_dispatch(const GeomDev& g, dd_dtype dt, const OpSet& ops, int 
                                               parts, (const float2*)in, (float2*)out);
     return;
   }
-  if (g.Bv == 256 && g.Vc % 16 == 0) {   // block form, slab order over the blocks
+  if (!dirac_threads_read(g)) {   // block form, slab order over the blocks
     blk_dispatch(g, dt, ops, nrhs, in, out, st);
     return;
   }
@@ -484,7 +487,7 @@ void launch_dirac_f32_in(const GeomDev& g, const OpSet& ops64, int nrhs, const f
   const double flops = (double)g.V * nrhs * kDiracFlopsPerSite;
   const double2* L = (const double2*)ops64.links;
   const double2* C = (const double2*)ops64.clover;
-  if (g.Bv == 256 && g.Vc % 16 == 0) {
+  if (!dirac_threads_read(g)) {
     DD_TIMED("k_dirac", st, bytes, flops,
              (blk_launch<double, double2, float2, double2>(g, ops64, nrhs, in, out, st)));
     return;
