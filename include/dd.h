@@ -253,10 +253,10 @@ dd_status dd_mg_release_workspace(dd_mg* mg);
  *                     type, working vectors, D_c and odd-site inverses in FP64,
  *                     FP32 and, for half storage, the half type)
  *   scratch_bytes   : the most held on top of those two while dd_gauge_create or
- *                     dd_setup runs, with the Galerkin build at its least column
- *                     chunk (the build takes a larger chunk only out of half of
- *                     the budget then free, and none on 4^4 blocks, so this figure
- *                     is a sufficient margin)
+ *                     dd_setup runs: on blocks other than 4^4 with the Galerkin
+ *                     build at its least column chunk (it takes a larger chunk
+ *                     only out of half of the budget then free, so this figure
+ *                     is a sufficient margin); the build takes none on 4^4 blocks
  *   workspace_bytes : the dd_solve workspace for nrhs right-hand sides
  * DD_ESHAPE / DD_EINVAL as dd_gauge_create and dd_setup would return them. */
 typedef struct {

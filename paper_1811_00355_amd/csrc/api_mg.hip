@@ -958,7 +958,7 @@ static dd_status build(dd_mg* mg, hipStream_t st) {
   const long long vbytes = 12LL * G.V * (long long)sizeof(double2);
   int chunk = 0;
   double2* W = nullptr;
-  if (galerkin_direct(G)) {
+  if (galerkin_direct(G.b)) {
     launch_galerkin(G, g->ops[DD_F64], mg->vstore, mg->n, Pb, mg->Dc64, st);
   } else {
     const size_t used = ctx_in_use(mg->ctx), free_b = mg->ctx->budget > used ? mg->ctx->budget - used : 0;
@@ -1403,16 +1403,13 @@ dd_status dd_footprint_bytes(const dd_problem* prob, const dd_mg_params* p, int 
                  (16 + 8) * blocks;
   if (st == DD_F16 || st == DD_BF16) setup += 4 * blocks;
   // scratch while a setup runs: the V-cycle workspace for the n vectors, the
-  // build's flag, then the Galerkin chunk or, for a half P, the FP32 copy of up to
-  // 1 GiB that a caller's budget has always been asked to leave (neither is taken on
-  // 4^4 blocks)
+  // build's flag and, where the build needs scratch vectors, their least chunk
   const WsShape sh{V, Vc, Vc / 2, (int)nc, p->coarse_restart, p->fgmres_restart, vt};
   const long long vbytes = 12 * V * (long long)sizeof(double2);
   long long chunk = std::min<long long>((long long)((4ULL << 30) / (size_t)vbytes), nc);
   if (chunk >= 16 && chunk < nc) chunk -= chunk % 16;
   if (chunk < 1) chunk = 1;
-  const size_t stage = (st == DD_F16 || st == DD_BF16) ? sizeof(float2) * (size_t)std::min<long long>(1LL << 27, nfine) : 0;
-  const size_t build = std::max<size_t>(stage, (size_t)chunk * vbytes);
+  const size_t build = galerkin_direct(prob->block) ? 0 : (size_t)chunk * vbytes;
   const size_t upload = 16 * 36ULL * V;   // dd_gauge_create stages the canonical links
   out->gauge_bytes = gauge;
   out->setup_bytes = setup;

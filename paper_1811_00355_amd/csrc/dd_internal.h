@@ -458,8 +458,10 @@ void launch_gram_schmidt(const GeomDev& g, dd_dtype vt, int n, const void* in, d
                          hipStream_t st);
 void launch_coarse_build(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P,
                          double2* Dc64, double2* W, int chunk, hipStream_t st);
-// the same without the scratch vectors, for 4^4 aggregates (galerkin_direct)
-bool galerkin_direct(const GeomDev& g);
+// the same without the scratch vectors, for 4^4 aggregates
+inline bool galerkin_direct(const int* block) {
+  return block[0] == 4 && block[1] == 4 && block[2] == 4 && block[3] == 4;
+}
 void launch_galerkin(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P, double2* Dc64,
                      hipStream_t st);
 void launch_coarse_invert(const GeomDev& g, int nc, const double2* Dc64, double2* Dinv64, int* bad_flag,

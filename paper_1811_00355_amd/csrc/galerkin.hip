@@ -338,10 +338,6 @@ void run_n(const GeomDev& g, const OpSet& ops64, int n, const void* P, double2* 
 
 }  // namespace
 
-bool galerkin_direct(const GeomDev& g) {
-  return g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4 && g.Vc % 8 == 0;
-}
-
 void launch_galerkin(const GeomDev& g, const OpSet& ops64, dd_dtype pst, int n, const void* P, double2* Dc64,
                      hipStream_t st) {
   switch (pst) {
