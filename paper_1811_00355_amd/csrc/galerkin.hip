@@ -112,8 +112,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
       for (int v = 0; v < 4; ++v) {
         double2* p = &sum[w][16 * rt + lk + 4 * v][li];
         const cx<double> o = acc[rt].get(v);
-        const double2 t = first ? make_double2(0.0, 0.0) : *p;
-        *p = make_double2(t.x + o.re, t.y + o.im);
+        if (first) {
+          *p = make_double2(o.re, o.im);
+        } else {   // the lane's own entry, added in the LDS: nothing to wait for
+          __hip_atomic_fetch_add(&p->x, o.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&p->y, o.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
       }
       acc[rt].zero();
     }
