@@ -210,7 +210,7 @@ __device__ __forceinline__ void hop_pairs(const GeomDev& g, const S* links, cons
 // leaves the CU its workgroups:
 // all eight faces in FP32 (48 KB), x and y in FP64 (72 KB; the z and t faces are whole
 // lines, and their blocks run far apart in the slab order).  Bound by traffic:
-// at 32^3x64, FP64, twelve right-hand sides, about 31 GB a launch (2.6 times the
+// at 32^3x64, FP64, twelve right-hand sides, 31.2 GB a launch (2.6 times the
 // algorithmic bytes) at 5.3 TB/s; two right-hand sides of a block in one workgroup
 // measured slower (7.2 against 6.1 ms).
 template <typename R, typename S, typename Tv, typename To, bool NT, int NF, bool FAR>
@@ -375,14 +375,16 @@ constexpr double kDiracFlopsPerSite = 1320.0 + 504.0 + 24.0;
 // Faces in LDS (the same bits as without): x and y in FP64, all in FP32, none for half
 // operands (their launch moves half the bytes, and the halos gave nothing), none on
 // lattices of at most 256 blocks, which run together anyway, so that the faces
-// would be one more latency, and none in FP64 for more than four right-hand sides on
-// up to 1024 blocks, whose vectors the last-level cache holds.  None either for blocks
+// would be one more latency, and none on FP64 spinors for more than four right-hand
+// sides on up to 1024 blocks.  (FP32 spinors under the FP64 operator, as the outer solver
+// applies it, gain there too.)  None either for blocks
 // of 256 sites with other edges than four, whose faces do not have face_load's 64
 // sites.  us, without / with faces: FP64 384 blocks (16^3x24) one right-hand side 33.7 / 31.9,
 // two 46.9 / 47.2, five 105 / 110, twelve 245 / 268; 768 (16^2x24x32) four 177 / 173, twelve 486 /
 // 517; 2592 (24^3x48) two 367 / 354, twelve 1797 / 1723; 32^3x64 one 733 / 697, twelve 6522 / 5862;
 // FP32 16^3x24 one 22.5 / 21.2, twelve 134 / 130, 24^3x48 117 / 107, 1128 / 1012; 8^4 FP32 13.1 / 14.1,
-// FP64 14.1 / 15.8.
+// FP64 14.1 / 15.8.  FP64 operator on FP32 spinors within a solve: 16^3x32 five 139 / 132, twelve 295 / 279,
+// 16^2x32^2 twelve 620 / 574.
 template <typename R, typename S, typename Tv, typename To>
 void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, void* out, hipStream_t st) {
   const unsigned nb = xcd_grid(g.Vc, nrhs);
@@ -391,7 +393,7 @@ void blk_launch(const GeomDev& g, const OpSet& ops, int nrhs, const void* in, vo
   constexpr bool F64 = sizeof(R) == 8;
   constexpr int NF = F64 ? 4 : sizeof(S) == 8 ? 8 : 0;
   const bool faces = g.Vc > 256 && g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && g.b[3] == 4 &&
-                     (!F64 || nrhs <= 4 || g.Vc > 1024);
+                     (sizeof(Tv) == 8 || nrhs <= 4 || g.Vc > 1024);
   auto* fn = nrhs == 1 ? (faces ? k_dirac_blk<R, S, Tv, To, true, NF, false> : k_dirac_blk<R, S, Tv, To, true, 0, false>)
              : !faces  ? k_dirac_blk<R, S, Tv, To, false, 0, false>
              : F64 && nrhs > 4 ? k_dirac_blk<R, S, Tv, To, false, NF, F64>

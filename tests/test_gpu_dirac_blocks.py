@@ -69,6 +69,33 @@ def test_batches_around_the_face_rules_same_bits(L, dtype):
     ctx.close()
 
 
+def test_solve_alone_and_in_a_batch_same_bits_on_384_blocks():
+    """The outer operator (FP64 on FP32 spinors, and FP64 on FP64 at the restarts) takes other face forms for one to four
+    right-hand sides than for six: the solutions are the same bits."""
+    import torch
+    from paper_1811_00355_amd import Context, Gauge, MG, default_params
+    from workloads import su3_random
+    L = (16, 16, 16, 24)
+    V = int(np.prod(L))
+    ctx = Context(0)
+    g = Gauge(ctx, L, (4, 4, 4, 4), np.resize(su3_random(4096 * 4 + 12, 0.2, 7), (V * 4, 3, 3)).reshape(V, 4, 3, 3), -0.1, 1.0)
+    mg = MG(g, default_params(block=(4, 4, 4, 4), n_vec=8, setup_iters=1, inner_dtype=1, store_dtype=3, seed=5))
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    b = torch.randn((6, V * 12), generator=gen, device="cuda", dtype=torch.complex128)
+    out = []
+    for n in (6, 3, 1):
+        print(f"solve L={L} nrhs={n}", flush=True)
+        x = torch.zeros_like(b[:n])
+        info, _ = mg.dd_solve(n, b[:n].contiguous(), x, 1e-8)
+        torch.cuda.synchronize()
+        assert all(i["converged"] for i in info[:n])
+        out.append(x)
+        assert torch.equal(x, out[0][:n])
+    mg.destroy()
+    g.destroy()
+    ctx.close()
+
+
 def test_solve_on_other_blocks_of_256_sites():
     import torch
     import _gpu
