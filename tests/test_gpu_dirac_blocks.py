@@ -69,6 +69,27 @@ def test_batches_around_the_face_rules_same_bits(L, dtype):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", [2, 3])
+def test_half_operands_alone_and_in_a_batch_same_bits(dtype):
+    """One right-hand side takes the form of the other operand types, several the one that keeps the operator in registers."""
+    import torch
+    from paper_1811_00355_amd import Context, Gauge
+    from workloads import su3_field
+    L, n = (8, 8, 8, 16), 5
+    ctx = Context(0)
+    g = Gauge(ctx, L, (4, 4, 4, 4), su3_field(L, 0.3, 11), -0.1, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn((n, 12, int(np.prod(L))), generator=gen, device="cuda", dtype=torch.complex64)
+    y, one = torch.empty_like(x), torch.empty_like(x[:1])
+    g.dd_dirac_apply(dtype, n, x, y)
+    for r in range(n):
+        g.dd_dirac_apply(dtype, 1, x[r:r + 1].contiguous(), one)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], y[r])
+    g.destroy()
+    ctx.close()
+
+
 def test_solve_alone_and_in_a_batch_same_bits_on_384_blocks():
     """The outer operator (FP64 on FP32 spinors, and FP64 on FP64 at the restarts) takes other face forms for one to four
     right-hand sides than for six: the solutions are the same bits."""
