@@ -70,9 +70,9 @@ constexpr int kMfmaMaxNc = 48;
 // One accumulator set of a complex product on matrix cores, in FP32 (three real
 // products, Gauss: with A = a + ib and x = c + id, k1 += a (c + d), k2 +=
 // (a + b)(-d), k3 += (b - a) c, Re = k1 + k2, Im = k1 + k3) or FP64 (four real
-// products, chained: the matrix cores are not what bounds it, and the four keep
-// the rounding of the plain form).  row(lk, v): the row that element v of lane
-// group lk holds.
+// products, chained: the matrix cores are not what bounds it, and three would
+// add roundings of sums of entries; kFine below is about the length of the
+// chains).  row(lk, v): the row that element v of lane group lk holds.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <typename R> struct Cacc;
 template <> struct Cacc<float> {
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(64 * DS * ((NC + 15) / 16) / TW) k_coarse_mfma
   constexpr bool kTiled = sizeof(R) == 4;   // FP64 blocks are column major
   // FP64: two chains for a block's columns, added before they meet the other directions, and the self term last.  Against
   // 80 bits, 2n = 16 / 40: 1.60 / 2.27e-16, a plain sum by columns 1.53 / 2.18, one chain with the self term first 2.12 /
-  // 3.06 (thirds: 1.58 / 1.99, but 3-10 % of the time; halves 0-3 %)
+  // 3.06 (thirds: 1.58 / 1.99, but 3-10 % of the time; halves 0-4 %)
   constexpr bool kFine = sizeof(R) == 8;
   constexpr int P = kTiled ? tile_group(NC, (int)sizeof(Sd)) : 1;
   struct alignas(P * sizeof(Sd)) Pack {

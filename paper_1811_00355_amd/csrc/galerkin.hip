@@ -76,7 +76,7 @@ __device__ __forceinline__ void half_part(const Sites<Sp, NS>* s, int q, bool lo
 // the FP64 products do the matrix cores (54 of them per four sites, direction and 16
 // columns at 2n = 40; 47 % busy): half types take two packed neighbours to a load,
 // the others let the four lanes lk of a vector take neighbours of one line.
-// 16^3x32, 2n = 40, BF16 vectors: 1.44 ms, 1.88 with single sites in lexicographic
+// 16^3x32, 2n = 40, BF16 vectors: 1.43-1.49 ms, 1.88 with single sites in lexicographic
 // order (nine passes over all sites that wrote D lambda and restricted it: 7.9);
 // loads a whole step ahead of the products gave 1.41, but spilled in FP64.  New
 // mass on 16^4 before / after: FP64 2270 / 1966 us, FP32 1942 / 1680, BF16 1690 / 1516.
